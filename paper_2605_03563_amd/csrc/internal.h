@@ -185,6 +185,51 @@ void add_correction(double* phi, const void* e, bool e_f32, const Geom& G, hipSt
 void dense_to_split(const double* dense, void* split, bool f32, const Geom& G, hipStream_t st);
 void split_to_dense(const void* split, bool f32, double* dense, const Geom& G, hipStream_t st);
 
+// The levels of a cycle that one workgroup runs in one launch (kernels_tail.hip).
+constexpr int kTailLevels = 8;
+struct TailArgs {
+  int nl, nu1, nu2;
+  int clear;     // elements of the potentials, zeroed at the start
+  int N, parts;  // coarsest unknowns, threads per row of its inverse
+  int blocks;    // entries of the inverse's blocks
+  int staged;    // byte offset of their copy in LDS (0: too many for it)
+  int f, r;      // LDS offsets (elements) of the right-hand sides below the top and of the residual
+  size_t lds;    // bytes of LDS
+  struct {
+    int n;       // intervals
+    double h2, ih2;
+  } d[kTailLevels];
+};
+// arguments of a tail over the nl levels lev[0..nl), the last one the coarsest;
+// false when they do not fit one workgroup
+bool tail_args(const Geom* lev, int nl, bool f32, int nu1, int nu2, TailArgs& A);
+// lets the kernel for a top level of n intervals use a compute unit's whole
+// LDS on the current device
+bool tail_enable(bool f32, int C, int n);
+// the coarsest inverse (E^3 unknowns) in the basis of even and odd functions
+// along each axis: a table of the threads' rows, then its diagonal blocks
+// (tail_blocks_size(E) doubles in all)
+size_t tail_blocks_size(int E);
+void tail_blocks(int E, const std::vector<double>& inv, std::vector<double>& out);
+// x = one V(nu1, nu2) cycle for f from a zero guess; G: the tail's top level
+void tail_cycle(const void* f, void* x, bool f32, const Geom& G, const TailArgs& A, const double* pinv,
+                hipStream_t st);
+
+// One leg of a 7-point V-cycle level in one launch (kernels_legs.hip), for
+// nu in 1..2 on levels of up to kLegMax intervals.  Each reads one array and
+// writes the unknowns of another.
+constexpr int kLegMax = 64;
+bool legs_ok(const Geom& G, int nu1, int nu2);
+int leg_blocks(const Geom& G);  // partial sums leg_up writes
+// x = nu forward sweeps from xin (nullptr: a zero guess with zero ghosts),
+// fc = R (f - L x)
+void leg_down(const void* xin, void* x, const void* f, bool f32, const Geom& G, void* fc, const Geom& Gc, int nu,
+              hipStream_t st);
+// x = nu backward sweeps from xin + P e, the ghost values taken from `ghost`
+// (nullptr: zero); partial (when not null): partial sums of the squared residual
+void leg_up(const void* xin, void* x, const void* ghost, const void* f, bool f32, const Geom& G, const void* e,
+            const Geom& Gc, int nu, double* partial, hipStream_t st);
+
 // reductions: sum nb partials of each of nslots slots (stride kPartialCap)
 // into scal->v[dst + slot]
 void finish_sum(const double* partial, int nb, int nslots, Scalars* scal, int dst, hipStream_t st);

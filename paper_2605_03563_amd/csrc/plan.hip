@@ -547,7 +547,17 @@ void carve(poisson_plan_s* P, Carver& cv) {
     }
     const int E = o.coarsest - 1;
     P->ncoarse = E * E * E;
-    P->cinv = (double*)cv.take(sizeof(double) * (size_t)P->ncoarse * P->ncoarse);
+    // the longest tail of levels that fits one workgroup and starts from a
+    // zero guess (an FP64 cycle's finest level starts from the iterate)
+    P->tail = -1;
+    std::vector<Geom> gs;
+    for (const Level& L : P->lv) gs.push_back(L.G);
+    for (int l = P->mg32 ? 0 : 1; l + 1 < (int)gs.size() && P->tail < 0; ++l)
+      if (tail_args(gs.data() + l, (int)gs.size() - l, P->mg32, o.nu1, o.nu2, P->targs)) P->tail = l;
+    if (P->tail >= 0)
+      P->tinv = (double*)cv.take(sizeof(double) * tail_blocks_size(E));
+    else
+      P->cinv = (double*)cv.take(sizeof(double) * (size_t)P->ncoarse * P->ncoarse);
   }
 }
 
@@ -618,22 +628,27 @@ bool coarse_inverse_compute(int nc, double h, int order, std::vector<double>& in
 }
 
 // The exact coarsest inverse depends only on (intervals, spacing, stencil);
-// plans of the same shape share one host copy instead of refactorising.
-bool coarse_inverse(int nc, double h, int order, std::vector<double>& inv) {
+// plans of the same shape share one host copy instead of refactorising: the
+// dense matrix, or its blocks for the kernel of the coarse levels.
+bool coarse_inverse(int nc, double h, int order, bool blocks, std::vector<double>& out) {
   static std::mutex mu;
-  static std::map<std::tuple<int, double, int>, std::vector<double>> cache;
-  const auto key = std::make_tuple(nc, h, order);
+  static std::map<std::tuple<int, double, int, bool>, std::vector<double>> cache;
+  const auto key = std::make_tuple(nc, h, order, blocks);
   {
     std::lock_guard<std::mutex> lk(mu);
     auto it = cache.find(key);
     if (it != cache.end()) {
-      inv = it->second;
+      out = it->second;
       return true;
     }
   }
-  if (!coarse_inverse_compute(nc, h, order, inv)) return false;
+  if (!coarse_inverse_compute(nc, h, order, out)) return false;
+  if (blocks) {
+    const std::vector<double> inv = std::move(out);
+    tail_blocks(nc - 1, inv, out);
+  }
   std::lock_guard<std::mutex> lk(mu);
-  cache[key] = inv;
+  cache[key] = out;
   return true;
 }
 
@@ -813,15 +828,33 @@ void w4_matrix(const W4& w, int n, std::vector<double>& A) {
 // pre-smoothing (last colour 1) only colour-0 residuals are restricted.  On
 // every level the correction skips the last colour, since the first
 // post-smoothing pass (that colour) reads none of its values and overwrites
-// them all.
-void vcycle(poisson_plan_s* P, int l, bool zero_guess, hipStream_t st) {
+// them all.  The levels from P->tail down run in one launch.
+// Returns the array that holds the result: the level's phi, or its tmp where
+// the way up wrote there.  norm (finest level, when the way up forms it):
+// partial sums of the squared residual.
+const void* vcycle(poisson_plan_s* P, int l, bool zero_guess, hipStream_t st, double* norm = nullptr) {
   Level& L = P->lv[l];
   const bool f32 = P->mg32;
   const poisson_opts_t& o = P->opts;
   const int C = P->C;
+  if (l == P->tail && zero_guess) {
+    tail_cycle(L.f, L.phi, f32, L.G, P->targs, P->tinv, st);
+    return L.phi;
+  }
   if (l + 1 == (int)P->lv.size()) {
     coarse_solve(P->cinv, L.f, L.phi, f32, L.G, st);
-    return;
+    return L.phi;
+  }
+  if (legs_ok(L.G, o.nu1, o.nu2)) {
+    // from a zero guess down into phi and up into tmp; from the iterate down
+    // into tmp and up into phi, which holds the ghost values
+    Level& Lc = P->lv[l + 1];
+    void* mid = zero_guess ? L.phi : L.tmp;
+    void* out = zero_guess ? L.tmp : L.phi;
+    leg_down(zero_guess ? nullptr : L.phi, mid, L.f, f32, L.G, Lc.f, Lc.G, o.nu1, st);
+    const void* e = vcycle(P, l + 1, true, st);
+    leg_up(mid, out, zero_guess ? nullptr : L.phi, L.f, f32, L.G, e, Lc.G, o.nu2, norm, st);
+    return out;
   }
   if (zero_guess && o.nu1 == 0) zero_unknowns(L.phi, f32, L.G, st);
   for (int s = 0; s < o.nu1; ++s)
@@ -841,10 +874,11 @@ void vcycle(poisson_plan_s* P, int l, bool zero_guess, hipStream_t st) {
     residual(L.phi, L.f, f32, L.tmp, f32, L.G, P->order, false, nullptr, st);
     restrict_fw(L.tmp, L.G, Lc.f, Lc.G, f32, st, C == 4 && o.nu1 > 0);
   }
-  vcycle(P, l + 1, true, st);
-  prolong_add(Lc.phi, Lc.G, L.phi, L.G, f32, st, o.nu2 > 0);
+  const void* e = vcycle(P, l + 1, true, st);
+  prolong_add(e, Lc.G, L.phi, L.G, f32, st, o.nu2 > 0);
   for (int s = 0; s < o.nu2; ++s)
     for (int c = C - 1; c >= 0; --c) colour_pass(L.phi, L.f, f32, L.G, P->order, c, 1.0, st);
+  return L.phi;
 }
 
 // One FP32 V(nu1, nu2) cycle of the spherical preconditioner from level l on a
@@ -973,12 +1007,15 @@ void spai_step(poisson_plan_s* P, hipStream_t st) {
 // V-cycle for the correction e of the current FP32 residual r32, phi64 += e,
 // and the new FP64 residual, stored as FP32 for the next step.
 void mg_step(poisson_plan_s* P, hipStream_t st) {
-  const int nb = residual_blocks(P->G0);
+  int nb = residual_blocks(P->G0);
   if (P->mg32) {
     Level& L0 = P->lv[0];
-    vcycle(P, 0, true, st);
-    add_correction(P->phi64, L0.phi, true, P->G0, st);
+    const void* e = vcycle(P, 0, true, st);
+    add_correction(P->phi64, e, true, P->G0, st);
     residual(P->phi64, P->f64, false, L0.f, true, P->G0, P->order, false, P->partial, st);
+  } else if (P->lv.size() > 1 && legs_ok(P->G0, P->opts.nu1, P->opts.nu2)) {
+    vcycle(P, 0, false, st, P->partial);
+    nb = leg_blocks(P->G0);
   } else {
     vcycle(P, 0, false, st);
     // the cycle ends with a Gauss-Seidel pass over colour 0 on two-colour
@@ -1055,8 +1092,8 @@ void cycle_tail(poisson_plan_s* P, hipStream_t st) {
   Level& Lc = P->lv[1];
   const poisson_opts_t& o = P->opts;
   if (!resrestrict19_ok(L.G)) restrict_fw(L.tmp, L.G, Lc.f, Lc.G, false, st, P->C == 4);
-  vcycle(P, 1, true, st);
-  prolong_add(Lc.phi, Lc.G, L.phi, L.G, false, st, o.nu2 > 0);
+  const void* e = vcycle(P, 1, true, st);
+  prolong_add(e, Lc.G, L.phi, L.G, false, st, o.nu2 > 0);
   for (int s = 0; s < o.nu2; ++s)
     for (int c = P->C - 1; c >= 0; --c) colour_pass(L.phi, L.f, false, L.G, P->order, c, 1.0, st);
 }
@@ -1871,11 +1908,17 @@ int poisson_plan(poisson_plan_t* out, const poisson_grid_t* grid, const poisson_
   } else if (!P->lv.empty()) {
     const Level& Lc = P->lv.back();
     std::vector<double> inv;
-    if (!coarse_inverse(Lc.G.n, Lc.G.h, P->order, inv)) {
+    const bool tail = P->tail >= 0;
+    if (!coarse_inverse(Lc.G.n, Lc.G.h, P->order, tail, inv)) {
       set_error("coarsest-level factorisation failed");
       return fail(POISSON_ENUMERIC);
     }
-    if (hipMemcpyAsync(P->cinv, inv.data(), sizeof(double) * inv.size(), hipMemcpyHostToDevice, st) != hipSuccess ||
+    if (tail && !tail_enable(P->mg32, P->C, P->lv[P->tail].G.n)) {
+      set_error("setup of the coarse levels' kernel failed");
+      return fail(POISSON_EHIP);
+    }
+    if (hipMemcpyAsync(tail ? P->tinv : P->cinv, inv.data(), sizeof(double) * inv.size(), hipMemcpyHostToDevice,
+                       st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess) {
       set_error("upload of the coarsest inverse failed");
       return fail(POISSON_EHIP);

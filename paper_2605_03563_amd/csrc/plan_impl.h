@@ -50,6 +50,11 @@ struct poisson_plan_s {
   bool mg32 = false;
   double* cinv = nullptr;
   int ncoarse = 0;
+  // levels tail .. run in one workgroup (-1: none fit, and cinv serves the
+  // coarsest level); its arguments and the coarsest inverse's blocks
+  int tail = -1;
+  psn::TailArgs targs{};
+  double* tinv = nullptr;
   // SPAI multigrid (natural layout)
   std::vector<psn::NLevel> nlv;
   // CG
