@@ -124,6 +124,28 @@ struct W4 {
 // Per-plan device scalars used by the Krylov solvers and reductions.
 struct Scalars {
   double v[32];
+  unsigned seq;  // number of the last post
+  int stop;      // the residual has met the solve's tolerance
+};
+
+// A kernel that finishes a reduction posts scalars for a host that waits:
+// pinned host memory that the host watches.  A transfer after the kernel and
+// the wait for the stream took 8-10 us per iteration, as long as a small
+// grid's iteration itself.  A value travels as two words, each half of it
+// beside the post's number in one 8-byte store, so that no word needs to be
+// ordered after another; kPostSlots posts may be underway.
+//
+// stop > 0: the scalar `first` is a squared residual norm, and Scalars::stop
+// is set once its root is at most stop times the root of v[kBnorm2] -- the
+// host's own test, for iterations that are queued before the host has made it.
+constexpr int kBnorm2 = 8;  // ||b||^2
+constexpr int kRes2 = 9;    // ||r||^2
+constexpr int kPostMax = 8, kPostSlots = 4;
+struct Post {
+  unsigned long long* mail = nullptr;  // nullptr: no post
+  int first = 0, count = 0;            // scalars posted
+  unsigned set = 0;                    // != 0: a solve's first post, with this number; else the last one's plus one
+  double stop = 0.0;
 };
 
 // ---------------------------------------------------------------------------
@@ -139,9 +161,10 @@ void zero_unknowns(void* x, bool f32, const Geom& G, hipStream_t st);
 
 // one colour pass of Gauss-Seidel / SOR in place (order 2: 7-point, order 6:
 // star); colours whose bit is set in zmask are read as zero (first sweep on a
-// zero initial guess, which then needs no separate clearing pass)
+// zero initial guess, which then needs no separate clearing pass).  stop (SOR,
+// omega != 1): a device flag that, once set, makes the pass leave phi alone
 void colour_pass(void* phi, const void* f, bool f32, const Geom& G, int order, int colour,
-                 double omega, hipStream_t st, int zmask = 0);
+                 double omega, hipStream_t st, int zmask = 0, const int* stop = nullptr);
 
 // Four-colour levels from 128 intervals (FP64, or FP32 when f32): the
 // 19-point residual fused with full weighting into f_coarse, without storing
@@ -231,8 +254,8 @@ void leg_up(const void* xin, void* x, const void* ghost, const void* f, bool f32
             const Geom& Gc, int nu, double* partial, hipStream_t st);
 
 // reductions: sum nb partials of each of nslots slots (stride kPartialCap)
-// into scal->v[dst + slot]
-void finish_sum(const double* partial, int nb, int nslots, Scalars* scal, int dst, hipStream_t st);
+// into scal->v[dst + slot], and post the scalars
+void finish_sum(const double* partial, int nb, int nslots, Scalars* scal, int dst, hipStream_t st, Post post = Post());
 
 // CG (A = -L, zero-ghost direction vectors, split layout, FP64).  The
 // direction is p_new = sr r + beta p_old (sr = 1: CG on r; sr = -1: PCG on
@@ -249,7 +272,7 @@ void pcg_dot(const double* r, const double* z, const Geom& G, double* partial, h
 int colour_pass_dot(double* phi, const double* f, const Geom& G, int colour, double* partial, hipStream_t st);
 void cg_update(double* x, double* r, const double* p, const double* q, const Geom& G, const Scalars* scal,
                double* partial, hipStream_t st);
-void cg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipStream_t st);
+void cg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipStream_t st, Post post = Post());
 int cg_blocks(const Geom& G);
 
 // multipole (Section 2.2)
@@ -337,7 +360,7 @@ void sph_prolong_add32(const SLev& Lc, const SLev& Lf, hipStream_t st);
 void sph_coarse32(const double* inv, const SLev& L, hipStream_t st);
 void sph_cast_in(const double* x, const SGeom& S, const SLev& L0, hipStream_t st);
 void sph_cast_out(const SLev& L0, double* x, const SGeom& S, hipStream_t st);
-void bicg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipStream_t st);
+void bicg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipStream_t st, Post post = Post());
 // SPAI multigrid on natural-layout levels (27-point stencils).
 NGeom make_ngeom(int n, double h);
 long long n27_blocks(const NGeom& G);

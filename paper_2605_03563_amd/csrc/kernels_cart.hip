@@ -108,10 +108,12 @@ __device__ inline void store_stream(T* p, T v) { __builtin_nontemporal_store(v, 
 // loads in flight at once.  ZG: zero initial guess -- the other colour is
 // taken as 0 (first pass of a cycle on a zeroed correction).  DOT: also the
 // block's partial sum of -(f . x_new) over the updated nodes (the PCG inner
-// product when F holds the CG residual and X the preconditioned one).
+// product when F holds the CG residual and X the preconditioned one).  stop
+// (SOR): when not null and set, X stays as it is.
 template <typename T, bool SOR, bool ZG, int KZP, bool DOT>
 __global__ __launch_bounds__(256) void k_pass7(T* __restrict__ X, const T* __restrict__ F, Geom G, int c,
-                                               T omega, T h2, double* __restrict__ partial) {
+                                               T omega, T h2, double* __restrict__ partial,
+                                               const int* __restrict__ stop) {
   int bx, by, bz;
   xcd_block(bx, by, bz);
   const int m = G.mlo() + bx * BX + (int)threadIdx.x;
@@ -137,6 +139,7 @@ __global__ __launch_bounds__(256) void k_pass7(T* __restrict__ X, const T* __res
 #pragma unroll
     for (int t = 0; t < KZP + 2; ++t) z[t] = ZG ? (T)0 : xo[(long long)min(k0 - 1 + t, k1 + 1) * plane];
     T xs[KZP], ym[KZP], yp[KZP], fv[KZP], old[KZP];
+    const bool stopped = SOR && stop && *stop;
 #pragma unroll
     for (int t = 0; t < KZP; ++t) {
       const int k = min(k0 + t, k1);
@@ -159,9 +162,9 @@ __global__ __launch_bounds__(256) void k_pass7(T* __restrict__ X, const T* __res
         if (!ZG) s = z[t + 1] + xs[t] + ym[t] + yp[t] + z[t] + z[t + 2];
         const T gs = (s - h2 * fv[t]) * sixth;
         T* __restrict__ dst = xc + (long long)k * plane;
-        if (SOR)
-          *dst = ((T)1 - omega) * old[t] + omega * gs;
-        else
+        if (SOR) {
+          if (!stopped) *dst = ((T)1 - omega) * old[t] + omega * gs;
+        } else
           store_stream(dst, gs);
         if constexpr (DOT) acc += (double)fv[t] * (double)gs;
       }
@@ -1715,12 +1718,13 @@ __global__ __launch_bounds__(256) void k_dense_split(const double* __restrict__ 
 
 // ---------------------------------------------------------------- reductions
 __global__ __launch_bounds__(kFinishThreads) void k_finish(const double* __restrict__ partial, int nb, int nslots,
-                                                           Scalars* __restrict__ scal, int dst) {
+                                                           Scalars* __restrict__ scal, int dst, Post post) {
   for (int slot = 0; slot < nslots; ++slot) {
     const double s = sum_partials(partial + slot * kPartialCap, nb);
     if (threadIdx.x == 0) scal->v[dst + slot] = s;
     __syncthreads();
   }
+  if (threadIdx.x == 0) post_scalars(scal, post);
 }
 
 // ---------------------------------------------------------------- CG (A = -L)
@@ -2060,17 +2064,20 @@ __global__ __launch_bounds__(256) void k_pcg_dot(const double* __restrict__ R, c
 // stage 0: v[4] = p.q (summed) -> alpha = rr / pq
 // stage 1: v[5] = new rr (summed) -> beta = rr_new / rr; rr = rr_new
 __global__ __launch_bounds__(kFinishThreads) void k_cg_scalars(const double* __restrict__ partial, int nb,
-                                                               Scalars* __restrict__ scal, int stage) {
+                                                               Scalars* __restrict__ scal, int stage, Post post) {
   const double s = sum_partials(partial, nb);
   if (threadIdx.x == 0) {
     if (stage == 0) {
       scal->v[4] = s;
-      scal->v[3] = (s != 0.0) ? scal->v[0] / s : 0.0;
+      // an iteration queued before the host saw the last residual leaves x as
+      // it is once that residual met the tolerance
+      scal->v[3] = (s != 0.0 && !scal->stop) ? scal->v[0] / s : 0.0;
     } else {
       scal->v[5] = s;
       scal->v[2] = (scal->v[0] != 0.0) ? s / scal->v[0] : 0.0;
       scal->v[0] = s;
     }
+    post_scalars(scal, post);
   }
 }
 
@@ -2131,11 +2138,11 @@ void zero_unknowns(void* x, bool f32, const Geom& G, hipStream_t st) {
 // planes per thread fixed at compile time: KZ on large levels, one on small
 template <typename T, bool SOR, bool ZG>
 static void pass7_kz(T* x, const T* f, const Geom& G, int colour, T omega, T h2, dim3 grid, dim3 blk,
-                     hipStream_t st) {
+                     hipStream_t st, const int* stop = nullptr) {
   if (kz_for(G) == KZ)
-    k_pass7<T, SOR, ZG, KZ, false><<<grid, blk, 0, st>>>(x, f, G, colour, omega, h2, nullptr);
+    k_pass7<T, SOR, ZG, KZ, false><<<grid, blk, 0, st>>>(x, f, G, colour, omega, h2, nullptr, stop);
   else
-    k_pass7<T, SOR, ZG, 1, false><<<grid, blk, 0, st>>>(x, f, G, colour, omega, h2, nullptr);
+    k_pass7<T, SOR, ZG, 1, false><<<grid, blk, 0, st>>>(x, f, G, colour, omega, h2, nullptr, stop);
 }
 
 // columns per lane of the vector 7-point pass: as many as make one 16-byte
@@ -2166,7 +2173,7 @@ static void pass7v_launch(T* x, const T* f, const Geom& G, int colour, bool zg, 
 
 template <typename T>
 static void pass7_launch(T* x, const T* f, const Geom& G, int colour, bool sor, bool zg, T omega, T h2, dim3 grid,
-                         dim3 blk, hipStream_t st) {
+                         dim3 blk, hipStream_t st, const int* stop) {
   if (!sor) {
     const int cpl = pass7_cpl<T>(G);
     if (cpl == 4) {
@@ -2176,7 +2183,7 @@ static void pass7_launch(T* x, const T* f, const Geom& G, int colour, bool sor, 
     }
   }
   if (sor)
-    pass7_kz<T, true, false>(x, f, G, colour, omega, h2, grid, blk, st);
+    pass7_kz<T, true, false>(x, f, G, colour, omega, h2, grid, blk, st, stop);
   else if (zg)
     pass7_kz<T, false, true>(x, f, G, colour, (T)1, h2, grid, blk, st);
   else
@@ -2184,7 +2191,7 @@ static void pass7_launch(T* x, const T* f, const Geom& G, int colour, bool sor, 
 }
 
 void colour_pass(void* phi, const void* f, bool f32, const Geom& G, int order, int colour, double omega,
-                 hipStream_t st, int zmask) {
+                 hipStream_t st, int zmask, const int* stop) {
   const dim3 grid = col_grid(G), blk(BX, BY);
   const double h2 = G.h * G.h;
   if (order == 2) {
@@ -2192,9 +2199,9 @@ void colour_pass(void* phi, const void* f, bool f32, const Geom& G, int order, i
     const bool zg = (zmask >> (colour ^ 1)) & 1;
     if (f32) {
       pass7_launch<float>((float*)phi, (const float*)f, G, colour, sor, zg, (float)omega, (float)h2, grid, blk,
-                          st);
+                          st, stop);
     } else {
-      pass7_launch<double>((double*)phi, (const double*)f, G, colour, sor, zg, omega, h2, grid, blk, st);
+      pass7_launch<double>((double*)phi, (const double*)f, G, colour, sor, zg, omega, h2, grid, blk, st, stop);
     }
   } else {
     // planes per run: long runs on the 511^3 level, where the window's reload
@@ -2230,9 +2237,9 @@ int colour_pass_dot(double* phi, const double* f, const Geom& G, int colour, dou
     return (int)nblocks(gv);
   }
   if (kz_for(G) == KZ)
-    k_pass7<double, false, false, KZ, true><<<grid, blk, 0, st>>>(phi, f, G, colour, 1.0, h2, partial);
+    k_pass7<double, false, false, KZ, true><<<grid, blk, 0, st>>>(phi, f, G, colour, 1.0, h2, partial, nullptr);
   else
-    k_pass7<double, false, false, 1, true><<<grid, blk, 0, st>>>(phi, f, G, colour, 1.0, h2, partial);
+    k_pass7<double, false, false, 1, true><<<grid, blk, 0, st>>>(phi, f, G, colour, 1.0, h2, partial, nullptr);
   return (int)nblocks(grid);
 }
 
@@ -2458,8 +2465,9 @@ void split_to_dense(const void* split, bool f32, double* dense, const Geom& G, h
     k_dense_split<double><<<grid, dim3(BX, BY), 0, st>>>(dense, (double*)split, G, 0);
 }
 
-void finish_sum(const double* partial, int nb, int nslots, Scalars* scal, int dst, hipStream_t st) {
-  k_finish<<<1, kFinishThreads, 0, st>>>(partial, nb, nslots, scal, dst);
+void finish_sum(const double* partial, int nb, int nslots, Scalars* scal, int dst, hipStream_t st,
+                Post post) {
+  k_finish<<<1, kFinishThreads, 0, st>>>(partial, nb, nslots, scal, dst, post);
 }
 
 int cg_blocks(const Geom& G) { return (int)nblocks(col_grid(G)); }
@@ -2506,8 +2514,8 @@ void cg_update(double* x, double* r, const double* p, const double* q, const Geo
   k_cg_upd<<<col_grid(G), dim3(BX, BY), 0, st>>>(x, r, p, q, G, scal, partial);
 }
 
-void cg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipStream_t st) {
-  k_cg_scalars<<<1, kFinishThreads, 0, st>>>(partial, nb, scal, stage);
+void cg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipStream_t st, Post post) {
+  k_cg_scalars<<<1, kFinishThreads, 0, st>>>(partial, nb, scal, stage, post);
 }
 
 }  // namespace psn

@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void k_pbicg_xr(double* __restrict__ X, double
 // stage 0: alpha = rho / (rhat.v); stage 1: omega = (t.s)/(t.t);
 // stage 2: beta = (rho_new/rho)(alpha/omega), rho = rho_new, v[7] = r.r
 __global__ __launch_bounds__(kFinishThreads) void k_bicg_scalars(const double* __restrict__ partial, int nb,
-                                                                 Scalars* __restrict__ scal, int stage) {
+                                                                 Scalars* __restrict__ scal, int stage, Post post) {
   const double s0 = sum_partials(partial, nb);
   __syncthreads();
   const double s1 = stage > 0 ? sum_partials(partial + kPartialCap, nb) : 0.0;
@@ -263,6 +263,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_bicg_scalars(const double* _
       v[0] = s0;
       v[7] = s1;
     }
+    post_scalars(scal, post);
   }
 }
 
@@ -513,8 +514,8 @@ void pbicg_xr(double* x, double* r, const double* phat, const double* shat, cons
   k_pbicg_xr<<<sgrid(S), dim3(BX, BY), 0, st>>>(x, r, phat, shat, s, t, rhat, S, scal, partial);
 }
 
-void bicg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipStream_t st) {
-  k_bicg_scalars<<<1, kFinishThreads, 0, st>>>(partial, nb, scal, stage);
+void bicg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipStream_t st, Post post) {
+  k_bicg_scalars<<<1, kFinishThreads, 0, st>>>(partial, nb, scal, stage, post);
 }
 
 void sph_line_pass(const SLev& L, int colour, int zero_guess, hipStream_t st) {

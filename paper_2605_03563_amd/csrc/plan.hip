@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <array>
+#include <chrono>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -820,6 +821,24 @@ void w4_matrix(const W4& w, int n, std::vector<double>& A) {
 }
 
 // ------------------------------------------------------------ solver pieces
+// A post of scalars first .. first + count - 1 by a step of a solve (not counted
+// here: a recorded step is enqueued later and more than once).
+Post step_post(const poisson_plan_s* P, int first = kRes2, int count = 1) {
+  Post p;
+  p.mail = P->mail;
+  p.first = first;
+  p.count = count;
+  return p;
+}
+
+// the first post of a solve: ||b||^2 and the initial ||r||^2
+Post first_post(poisson_plan_s* P) {
+  Post p = step_post(P, kBnorm2, 2);
+  if (++P->posted == 0) ++P->posted;
+  p.set = P->posted;
+  return p;
+}
+
 // One V(nu1, nu2) cycle from level l down.  zero_guess: the level's
 // unknowns start at zero (every coarse correction, and the FP32 correction of
 // a refinement step), so the first forward sweep reads colours it has not yet
@@ -927,7 +946,7 @@ void sph_mg_iteration(poisson_plan_s* P, double* phi, hipStream_t st) {
   pbicg_apply(shat, P->stt, P->ss, 1, S, P->sc, P->partial, st);
   bicg_scalars(P->partial, nb, P->scal, 1, st);
   pbicg_xr(phi, P->sr, phat, shat, P->ss, P->stt, P->srh, S, P->scal, P->partial, st);
-  bicg_scalars(P->partial, nb, P->scal, 2, st);
+  bicg_scalars(P->partial, nb, P->scal, 2, st, step_post(P, 0, 8));
 }
 
 // Stream on which the plan's graphs are recorded: the caller's capture
@@ -995,18 +1014,18 @@ void spai_vcycle(poisson_plan_s* P, int l, hipStream_t st) {
   if (cur != L.u) n_copy(cur, L.u, L.f32, L.G, st);
 }
 
-void spai_step(poisson_plan_s* P, hipStream_t st) {
+void spai_step(poisson_plan_s* P, hipStream_t st, const Post& post) {
   NLevel& L = P->nlv[0];
   spai_vcycle(P, 0, st);
   n27_residual(L.u, L.f, nullptr, false, L.G, L.A, true, P->partial, st);
-  finish_sum(P->partial, (int)n27_blocks(L.G), 1, P->scal, kRes2, st);
+  finish_sum(P->partial, (int)n27_blocks(L.G), 1, P->scal, kRes2, st, post);
 }
 
 // One multigrid iteration followed by the fine residual norm into
 // scal->v[kRes2].  MG: a V-cycle on (phi64; f64).  MG_IR32: the FP32
 // V-cycle for the correction e of the current FP32 residual r32, phi64 += e,
 // and the new FP64 residual, stored as FP32 for the next step.
-void mg_step(poisson_plan_s* P, hipStream_t st) {
+void mg_step(poisson_plan_s* P, hipStream_t st, const Post& post) {
   int nb = residual_blocks(P->G0);
   if (P->mg32) {
     Level& L0 = P->lv[0];
@@ -1023,7 +1042,7 @@ void mg_step(poisson_plan_s* P, hipStream_t st) {
     const int col = (P->C == 2 && P->opts.nu2 > 0 && P->lv.size() > 1) ? 1 : -1;
     residual(P->phi64, P->f64, false, nullptr, false, P->G0, P->order, false, P->partial, st, col);
   }
-  finish_sum(P->partial, nb, 1, P->scal, kRes2, st);
+  finish_sum(P->partial, nb, 1, P->scal, kRes2, st, post);
 }
 
 // Record what fn enqueues on the capture stream into *exec (once).
@@ -1052,9 +1071,9 @@ int capture_into(poisson_plan_s* P, hipGraphExec_t* exec, Fn fn) {
 int capture_step(poisson_plan_s* P) {
   return capture_into(P, &P->step_exec, [P](hipStream_t cs) {
     if (!P->nlv.empty())
-      spai_step(P, cs);
+      spai_step(P, cs, step_post(P));
     else
-      mg_step(P, cs);
+      mg_step(P, cs, step_post(P));
   });
 }
 
@@ -1081,7 +1100,7 @@ void cycle_head(poisson_plan_s* P, hipStream_t st) {
   } else {
     residual(L.phi, L.f, false, L.tmp, false, L.G, P->order, false, P->partial, st);
   }
-  finish_sum(P->partial, nb, 1, P->scal, kRes2, st);
+  finish_sum(P->partial, nb, 1, P->scal, kRes2, st, step_post(P));
 }
 
 // tail of a cycle: restriction of the head's residual (the last colour's
@@ -1124,9 +1143,9 @@ int launch_split(poisson_plan_s* P, bool first) {
 int launch_step(poisson_plan_s* P) {
   if (!capture_stream(P)) {
     if (!P->nlv.empty())
-      spai_step(P, P->st);
+      spai_step(P, P->st, step_post(P));
     else
-      mg_step(P, P->st);
+      mg_step(P, P->st, step_post(P));
     return launch_check("multigrid step");
   }
   CHK(capture_step(P));
@@ -1137,6 +1156,40 @@ int launch_step(poisson_plan_s* P) {
 int read_scalars(poisson_plan_s* P, int first, int count) {
   HIPCHK(hipMemcpyAsync(P->host, &P->scal->v[first], sizeof(double) * count, hipMemcpyDeviceToHost, P->st));
   HIPCHK(hipStreamSynchronize(P->st));
+  return POISSON_OK;
+}
+
+// Waits for post number seq of `count` scalars and leaves them in P->host.  The
+// host looks at the pinned memory for as long as a short iteration takes, and
+// sleeps on the stream after that.
+int wait_post(poisson_plan_s* P, unsigned seq, int count) {
+  const unsigned long long* slot = P->mail + (seq % kPostSlots) * (2 * kPostMax);
+  unsigned long long w[2 * kPostMax];
+  auto here = [&] {
+    for (int i = 0; i < 2 * count; ++i) {
+      w[i] = __atomic_load_n(slot + i, __ATOMIC_RELAXED);
+      if ((unsigned)(w[i] >> 32) != seq) return false;
+    }
+    return true;
+  };
+  const auto start = std::chrono::steady_clock::now();
+  bool got = here();
+  while (!got && std::chrono::steady_clock::now() - start < std::chrono::microseconds(300))
+    for (int i = 0; i < 32 && !got; ++i) {
+      __builtin_ia32_pause();
+      got = here();
+    }
+  if (!got) {
+    HIPCHK(hipStreamSynchronize(P->st));
+    if (!here()) {
+      set_error("a reduction's result did not arrive");
+      return POISSON_EHIP;
+    }
+  }
+  for (int i = 0; i < count; ++i) {
+    const unsigned long long v = w[2 * i] << 32 | (w[2 * i + 1] & 0xffffffffu);
+    memcpy(&P->host[i], &v, sizeof v);
+  }
   return POISSON_OK;
 }
 
@@ -1249,7 +1302,7 @@ int cart_setup_impl(poisson_plan_s* P, const double* rho, double* phi) {
     rout = P->cr;
   }
   residual(P->phi64, P->f64, false, rout, rout32, G, P->order, false, P->partial, st);
-  finish_sum(P->partial, nb, 1, P->scal, kRes2, st);
+  finish_sum(P->partial, nb, 1, P->scal, kRes2, st, first_post(P));
   return launch_check("solve setup");
 }
 
@@ -1271,9 +1324,9 @@ int solve_spai(poisson_plan_s* P, const double* rho, double* phi, double tol, po
   n_from_caller(phi, g.pitch[0], g.pitch[1], g.ghost, (double*)L.u, L.G, false, st);
   if (L.u2) n_from_caller(phi, g.pitch[0], g.pitch[1], g.ghost, (double*)L.u2, L.G, false, st);
   n27_residual(L.u, L.f, nullptr, false, L.G, L.A, true, P->partial, st);
-  finish_sum(P->partial, nb, 1, P->scal, kRes2, st);
+  finish_sum(P->partial, nb, 1, P->scal, kRes2, st, first_post(P));
   CHK(launch_check("SPAI setup"));
-  CHK(read_scalars(P, kBnorm2, 2));
+  CHK(wait_post(P, P->posted, 2));
   T.bnorm = sqrt(P->host[0]);
   double rel = rel_of(P->host[1], T.bnorm);
   T.push(rel);
@@ -1285,9 +1338,10 @@ int solve_spai(poisson_plan_s* P, const double* rho, double* phi, double tol, po
   bool conv = rel <= tol;
   while (!conv && it < o.max_iter) {
     CHK(launch_step(P));
+    ++P->posted;
     ++it;
     if (it % o.check_every == 0 || it == o.max_iter) {
-      CHK(read_scalars(P, kRes2, 1));
+      CHK(wait_post(P, P->posted, 1));
       rel = rel_of(P->host[0], T.bnorm);
       T.push(rel);
       if (!isfinite(rel)) {
@@ -1316,7 +1370,7 @@ int solve_cart(poisson_plan_s* P, const double* rho, double* phi, double tol, po
   const Geom& G = P->G0;
   const int nb = residual_blocks(G);
   CHK(cart_setup_impl(P, rho, phi));
-  CHK(read_scalars(P, kBnorm2, 2));
+  CHK(wait_post(P, P->posted, 2));
   T.bnorm = sqrt(P->host[0]);
   double rel = rel_of(P->host[1], T.bnorm);
   T.push(rel);
@@ -1326,36 +1380,81 @@ int solve_cart(poisson_plan_s* P, const double* rho, double* phi, double tol, po
   }
   int it = 0;
   bool conv = rel <= tol;
+  // Runs iterations step(check) until the residual posted by every
+  // check_every-th one meets the tolerance.  On small grids one iteration is
+  // queued ahead of the one whose residual the host waits for, since the host's
+  // look at it and the next launches took 8-12 us per iteration of 12-70; the
+  // iteration ahead finds Scalars::stop set and leaves the potential alone.
+  // From the ninth iteration on, so that a solve which needs few does not pay
+  // for one more; not above 4 million unknowns (157^3), where an iteration is
+  // longer than what that saves over a hundred.
+  bool may_lead = (double)(g.n[0] - 1) * (g.n[0] - 1) * (g.n[0] - 1) <= 4e6 && o.check_every <= 4;
+  auto iterate = [&](const char* what, const char* failure, auto&& step) -> int {
+    int sent = 0;
+    unsigned due[kPostSlots] = {};  // numbers of the posts awaited, oldest first
+    int last[kPostSlots] = {};      // iterations done by then
+    int waiting = 0;
+    while (!conv && it < o.max_iter) {
+      const int lead = may_lead && it >= 8 ? 2 : 1;
+      while (waiting < lead && sent < o.max_iter) {
+        bool check;
+        do {
+          ++sent;
+          check = sent % o.check_every == 0 || sent == o.max_iter;
+          step(check);
+        } while (!check);
+        ++P->posted;
+        due[waiting] = P->posted;
+        last[waiting++] = sent;
+        CHK(launch_check(what));
+      }
+      CHK(wait_post(P, due[0], 1));
+      it = last[0];
+      --waiting;
+      due[0] = due[1];
+      last[0] = last[1];
+      rel = rel_of(P->host[0], T.bnorm);
+      T.push(rel);
+      if (!isfinite(rel)) {
+        HIPCHK(hipStreamSynchronize(st));
+        set_error("%s %s (non-finite residual)", what, failure);
+        return POISSON_ENUMERIC;
+      }
+      conv = rel <= tol;
+    }
+    return POISSON_OK;
+  };
+  auto checked = [&](bool check, int scalar) {
+    Post p;
+    if (check) {
+      p = step_post(P, scalar);
+      p.stop = tol;
+    }
+    return p;
+  };
   if (o.method == POISSON_SOR) {
     const double rj = rjac(P);
     double w_opt = 2.0 / (1.0 + sqrt(1.0 - rj * rj));
     if (o.omega_mode == POISSON_OMEGA_OPT_A) w_opt = 2.0 / (1.0 + M_PI / g.n[0]);
     if (o.omega_mode == POISSON_OMEGA_FIXED) w_opt = o.omega;
     double wc = 1.0 / (1.0 - rj * rj / 2.0);  // Chebyshev sequence from n = 1
-    while (!conv && it < o.max_iter) {
+    // a pass with factor 1 is the Gauss-Seidel pass, which does not read the
+    // old value and takes no flag (two intervals: r_J = 0)
+    if (g.n[0] < 3 || (o.omega_mode != POISSON_OMEGA_CHEBYSHEV && w_opt == 1.0)) may_lead = false;
+    CHK(iterate("SOR", "diverged", [&](bool check) {
       for (int c = 0; c < 2; ++c) {
         double w = w_opt;
         if (o.omega_mode == POISSON_OMEGA_CHEBYSHEV) {
           w = wc;
           wc = 1.0 / (1.0 - rj * rj * wc / 4.0);
         }
-        colour_pass(P->phi64, P->f64, false, G, 2, c, w, st);
+        colour_pass(P->phi64, P->f64, false, G, 2, c, w, st, 0, &P->scal->stop);
       }
-      ++it;
-      if (it % o.check_every == 0 || it == o.max_iter) {
+      if (check) {
         residual(P->phi64, P->f64, false, nullptr, false, G, 2, false, P->partial, st);
-        finish_sum(P->partial, nb, 1, P->scal, kRes2, st);
-        CHK(launch_check("SOR"));
-        CHK(read_scalars(P, kRes2, 1));
-        rel = rel_of(P->host[0], T.bnorm);
-        T.push(rel);
-        if (!isfinite(rel)) {
-          set_error("SOR diverged (non-finite residual)");
-          return POISSON_ENUMERIC;
-        }
-        conv = rel <= tol;
+        finish_sum(P->partial, nb, 1, P->scal, kRes2, st, checked(true, kRes2));
       }
-    }
+    }));
   } else if (o.method == POISSON_PCG) {
     // z = M^-1 rho by one symmetric multi-colour Gauss-Seidel step on
     // L z = r (r = -rho) from z = 0; the direction is built from -z so the
@@ -1368,26 +1467,14 @@ int solve_cart(poisson_plan_s* P, const double* rho, double* phi, double tol, po
     fill_zero(P->cp0, false, G.total(), st);
     double* pold = P->cp0;
     double* pnew = P->cp1;
-    while (!conv && it < o.max_iter) {
+    CHK(iterate("PCG", "breakdown", [&](bool check) {
       cg_direction_apply(P->cz, pold, pnew, P->cq, G, P->order, P->scal, P->partial, st, -1.0);
       cg_scalars(P->partial, cg_dir_blocks(G, P->order), P->scal, 0, st);
       cg_update(P->phi64, P->cr, pnew, P->cq, G, P->scal, P->partial, st);
-      finish_sum(P->partial, cb, 1, P->scal, kRes2, st);
+      finish_sum(P->partial, cb, 1, P->scal, kRes2, st, checked(check, kRes2));
       cg_scalars(P->partial, pcg_precondition(P, st), P->scal, 1, st);
       std::swap(pold, pnew);
-      ++it;
-      if (it % o.check_every == 0 || it == o.max_iter) {
-        CHK(launch_check("PCG"));
-        CHK(read_scalars(P, kRes2, 1));
-        rel = rel_of(P->host[0], T.bnorm);
-        T.push(rel);
-        if (!isfinite(rel)) {
-          set_error("PCG breakdown (non-finite residual)");
-          return POISSON_ENUMERIC;
-        }
-        conv = rel <= tol;
-      }
-    }
+    }));
   } else if (o.method == POISSON_CG) {
     const int cb = cg_blocks(G);
     // rr = r.r ; beta = 0 ; p_old = 0
@@ -1397,32 +1484,21 @@ int solve_cart(poisson_plan_s* P, const double* rho, double* phi, double tol, po
     fill_zero(P->cp0, false, G.total(), st);
     double* pold = P->cp0;
     double* pnew = P->cp1;
-    while (!conv && it < o.max_iter) {
+    CHK(iterate("CG", "breakdown", [&](bool check) {
       cg_direction_apply(P->cr, pold, pnew, P->cq, G, P->order, P->scal, P->partial, st);
       cg_scalars(P->partial, cg_dir_blocks(G, P->order), P->scal, 0, st);
       cg_update(P->phi64, P->cr, pnew, P->cq, G, P->scal, P->partial, st);
-      cg_scalars(P->partial, cb, P->scal, 1, st);
+      cg_scalars(P->partial, cb, P->scal, 1, st, checked(check, kRR));
       std::swap(pold, pnew);
-      ++it;
-      if (it % o.check_every == 0 || it == o.max_iter) {
-        CHK(launch_check("CG"));
-        CHK(read_scalars(P, kRR, 1));
-        rel = rel_of(P->host[0], T.bnorm);
-        T.push(rel);
-        if (!isfinite(rel)) {
-          set_error("CG breakdown (non-finite residual)");
-          return POISSON_ENUMERIC;
-        }
-        conv = rel <= tol;
-      }
-    }
+    }));
   } else {  // multigrid
     const bool split = split_cycle(P);
     while (!conv && it < o.max_iter) {
       CHK(split ? launch_split(P, it == 0) : launch_step(P));
+      ++P->posted;
       ++it;
       if (it % o.check_every == 0 || it == o.max_iter) {
-        CHK(read_scalars(P, kRes2, 1));
+        CHK(wait_post(P, P->posted, 1));
         rel = rel_of(P->host[0], T.bnorm);
         T.push(rel);
         if (!isfinite(rel)) {
@@ -1500,9 +1576,10 @@ int solve_sph_sor(poisson_plan_s* P, const double* rho, double* phi, double tol,
     ++it;
     if (it % o.check_every == 0 || it == o.max_iter) {
       sph_residual(phi, rho, nullptr, S, P->sc, o.four_pi_G, false, P->partial, st);
-      finish_sum(P->partial, nb, 1, P->scal, kRes2, st);
+      finish_sum(P->partial, nb, 1, P->scal, kRes2, st, step_post(P));
+      ++P->posted;
       CHK(launch_check("spherical SOR"));
-      CHK(read_scalars(P, kRes2, 1));
+      CHK(wait_post(P, P->posted, 1));
       rel = rel_of(P->host[0], T.bnorm);
       T.push(rel);
       if (!isfinite(rel)) {
@@ -1533,9 +1610,9 @@ int solve_sph(poisson_plan_s* P, const double* rho, double* phi, double tol, poi
   sph_residual(phi, rho, nullptr, S, P->sc, o.four_pi_G, true, P->partial, st);
   finish_sum(P->partial, nb, 1, P->scal, kBnorm2, st);
   sph_residual(phi, rho, P->sr, S, P->sc, o.four_pi_G, false, P->partial, st);
-  finish_sum(P->partial, nb, 1, P->scal, kRes2, st);
+  finish_sum(P->partial, nb, 1, P->scal, kRes2, st, first_post(P));
   CHK(launch_check("spherical setup"));
-  CHK(read_scalars(P, kBnorm2, 2));
+  CHK(wait_post(P, P->posted, 2));
   T.bnorm = sqrt(P->host[0]);
   double rel = rel_of(P->host[1], T.bnorm);
   T.push(rel);
@@ -1584,13 +1661,14 @@ int solve_sph(poisson_plan_s* P, const double* rho, double* phi, double tol, poi
       pbicg_apply(shat, P->stt, P->ss, 1, S, P->sc, P->partial, st);
       bicg_scalars(P->partial, nb, P->scal, 1, st);
       pbicg_xr(phi, P->sr, phat, shat, P->ss, P->stt, P->srh, S, P->scal, P->partial, st);
-      bicg_scalars(P->partial, nb, P->scal, 2, st);
+      bicg_scalars(P->partial, nb, P->scal, 2, st, step_post(P, 0, 8));
     }
+    ++P->posted;
     ++it;
     if (!(it % o.check_every == 0 || it == o.max_iter)) continue;
     {
       CHK(launch_check("BiCGSTAB"));
-      CHK(read_scalars(P, 0, 8));
+      CHK(wait_post(P, P->posted, 8));
       const double rr = P->host[7];
       rel = rel_of(rr, T.bnorm);
       T.push(rel);
@@ -1636,7 +1714,7 @@ int psn::cart_step(poisson_plan_s* P, bool use_graph) {
     return POISSON_EINVAL;
   }
   if (use_graph) return launch_step(P);
-  mg_step(P, P->st);
+  mg_step(P, P->st, Post());
   return launch_check("multigrid step");
 }
 
@@ -1717,11 +1795,16 @@ int poisson_plan(poisson_plan_t* out, const poisson_grid_t* grid, const poisson_
     poisson_plan_destroy(P);
     return s;
   };
-  if (hipHostMalloc((void**)&P->host, 64 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+  // coherent: the host reads posts while kernels run
+  constexpr size_t host_bytes = (16 + kPostSlots * 2 * kPostMax) * sizeof(double);
+  if (hipHostMalloc((void**)&P->host, host_bytes, hipHostMallocMapped | hipHostMallocCoherent) !=
+      hipSuccess) {
     set_error("pinned host allocation failed");
     P->host = nullptr;
     return fail(POISSON_EHIP);
   }
+  memset(P->host, 0, host_bytes);
+  P->mail = reinterpret_cast<unsigned long long*>(P->host + 16);
   for (int i = 0; i < 3; ++i)
     if (hipEventCreate(&P->ev[i]) != hipSuccess) {
       set_error("event creation failed");
@@ -2203,14 +2286,14 @@ int poisson_op_vcycle(poisson_plan_t P, const double* d_rho, double* d_phi, int3
     n_rhs(d_rho, g.pitch[0], g.pitch[1], g.ghost, (double*)L.f, L.G, P->order, P->opts.four_pi_G, st);
     n_from_caller(d_phi, g.pitch[0], g.pitch[1], g.ghost, (double*)L.u, L.G, false, st);
     if (L.u2) n_from_caller(d_phi, g.pitch[0], g.pitch[1], g.ghost, (double*)L.u2, L.G, false, st);
-    for (int c = 0; c < cycles; ++c) spai_step(P, st);
+    for (int c = 0; c < cycles; ++c) spai_step(P, st, Post());
     n_to_caller((const double*)L.u, L.G, d_phi, g.pitch[0], g.pitch[1], g.ghost, st);
     return launch_check("poisson_op_vcycle");
   }
   split_from_natural(d_phi, g.pitch[0], g.pitch[1], P->phi64, false, P->G0, 1.0, st);
   split_from_natural(d_rho, g.pitch[0], g.pitch[1], P->f64, false, P->G0, P->opts.four_pi_G, st);
   if (P->mg32) residual(P->phi64, P->f64, false, P->lv[0].f, true, P->G0, P->order, false, nullptr, st);
-  for (int c = 0; c < cycles; ++c) mg_step(P, st);
+  for (int c = 0; c < cycles; ++c) mg_step(P, st, Post());
   merge_to_natural(P->phi64, d_phi, g.pitch[0], g.pitch[1], P->G0, true, 1.0, st);
   return launch_check("poisson_op_vcycle");
 }

@@ -86,6 +86,8 @@ struct poisson_plan_s {
   double* mom_tcoef = nullptr;
   double* mom_scratch = nullptr;
   double* host = nullptr; // pinned scalars
+  unsigned long long* mail = nullptr;  // pinned: the scalars posted by a solve's kernels (Post)
+  unsigned posted = 0;                 // number of the last post enqueued
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
   hipGraphExec_t step_exec = nullptr;
   // FP64 multigrid solves whose fine level stores its residual: the first
@@ -96,7 +98,7 @@ struct poisson_plan_s {
 
 namespace psn {
 
-enum ScalarSlot { kRR = 0, kBnorm2 = 8, kRes2 = 9 };
+constexpr int kRR = 0;  // r.r of the Krylov solvers (kBnorm2, kRes2: internal.h)
 
 // Asynchronous phases of a Cartesian multigrid solve on the plan's stream
 // (no host synchronisation): setup = multipole boundary (when lmax >= 0),

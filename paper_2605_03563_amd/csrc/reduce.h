@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "internal.h"
+
 namespace psn {
 
 constexpr long long kPartialCap = 1 << 16;  // partial-sum slots per reduction
@@ -69,6 +71,25 @@ __device__ inline double sum_partials(const double* __restrict__ p, int nb) {
   }
   for (; i < nb; i += T) a0 += p[i];
   return block_sum((a0 + a1) + (a2 + a3));
+}
+
+// Posts scalars (see Post); by the thread that wrote them.
+__device__ inline void post_scalars(Scalars* s, const Post& p) {
+  if (!p.mail) return;
+  const unsigned seq = p.set ? p.set : s->seq + 1;
+  s->seq = seq;
+  if (p.set) s->stop = 0;
+  if (p.stop > 0.0) {
+    const double b = sqrt(fmax(s->v[kBnorm2], 0.0)), r = sqrt(fmax(s->v[p.first], 0.0));
+    if ((b > 0.0 ? r / b : r) <= p.stop) s->stop = 1;
+  }
+  unsigned long long* slot = p.mail + (seq % kPostSlots) * (2 * kPostMax);
+  const unsigned long long tag = (unsigned long long)seq << 32;
+  for (int i = 0; i < p.count; ++i) {
+    const unsigned long long v = (unsigned long long)__double_as_longlong(s->v[p.first + i]);
+    __hip_atomic_store(slot + 2 * i, tag | (v >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(slot + 2 * i + 1, tag | (v & 0xffffffffu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 // threads of the one-block kernels that finish a reduction
