@@ -166,6 +166,13 @@ void zero_unknowns(void* x, bool f32, const Geom& G, hipStream_t st);
 void colour_pass(void* phi, const void* f, bool f32, const Geom& G, int order, int colour,
                  double omega, hipStream_t st, int zmask = 0, const int* stop = nullptr);
 
+// Gauss-Seidel pass of the 19-point star on large four-colour levels
+// (kernels_pass19.hip); pass19_enable lets its kernels use the LDS they need on
+// the current device
+bool pass19_ok(const Geom& G, bool f32);
+void pass19(void* phi, const void* f, bool f32, const Geom& G, int colour, int zmask, hipStream_t st);
+bool pass19_enable();
+
 // Four-colour levels from 128 intervals (FP64, or FP32 when f32): the
 // 19-point residual fused with full weighting into f_coarse, without storing
 // the fine residual; partial (when not null) receives partial sums of r^2,

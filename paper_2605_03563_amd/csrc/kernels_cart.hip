@@ -2204,9 +2204,9 @@ void colour_pass(void* phi, const void* f, bool f32, const Geom& G, int order, i
       pass7_launch<double>((double*)phi, (const double*)f, G, colour, sor, zg, omega, h2, grid, blk, st, stop);
     }
   } else {
-    // planes per run: long runs on the 511^3 level, where the window's reload
-    // at each run start costs bandwidth; shorter ones below, where the
-    // blocks of a pass must still fill the chip
+    if (pass19_ok(G, f32)) return pass19(phi, f, f32, G, colour, zmask, st);
+    // planes per run: one where a level is short of blocks, more on levels that
+    // the kernel above does not take
     const int E = G.n - 1;
     if (f32) {
       const int kz = G.n >= 512 ? 8 : G.n >= 128 ? 2 : 1;

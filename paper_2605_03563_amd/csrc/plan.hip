@@ -1810,6 +1810,10 @@ int poisson_plan(poisson_plan_t* out, const poisson_grid_t* grid, const poisson_
       set_error("event creation failed");
       return fail(POISSON_EHIP);
     }
+  if (!P->sph && P->C == 4 && !pass19_enable()) {
+    set_error("setup of the four-colour pass failed");
+    return fail(POISSON_EHIP);
+  }
   hipStream_t st = P->st;
   // zero the whole workspace once: ghosts of correction and direction
   // vectors must stay zero and are never written afterwards
