@@ -371,17 +371,21 @@ void bicg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipSt
 // SPAI multigrid on natural-layout levels (27-point stencils).
 NGeom make_ngeom(int n, double h);
 long long n27_blocks(const NGeom& G);
-// r = f - A u at the unknowns (r may be nullptr with norm); norm: one partial
-// sum of r^2 per block.  f32: the level is stored in FP32 (arithmetic FP64).
-void n27_residual(const void* u, const void* f, void* r, bool f32, const NGeom& G, const W4& A, bool norm,
-                  double* partial, hipStream_t st);
+// r = f - A u at the unknowns and one partial sum of r^2 per block
+// (n27_blocks of them)
+void n27_residual(const double* u, const double* f, double* r, const NGeom& G, const W4& A, double* partial,
+                  hipStream_t st);
+// partial sums of (f - A u)^2; returns how many
+int n27_norm(const double* u, const double* f, const NGeom& G, const W4& A, double* partial, hipStream_t st);
 // fused Richardson step out of place: out = u - M (f - A u) at the unknowns
-// (ghost entries of out are not written)
+// (ghost entries of out are not written); u nullptr: zero.  f32: the level is
+// stored in FP32 (arithmetic FP64).
 void n_spai_step(const void* u, const void* f, void* out, bool f32, const NGeom& G, const W4& A, const W4& M,
                  hipStream_t st);
+// fc = R (f - A u), full weighting without storing the residual
+void n_resrestrict(const void* u, const void* f, bool f32, const NGeom& G, const W4& A, void* fc, bool f32_coarse,
+                   const NGeom& Gc, hipStream_t st);
 void n_copy(const void* a, void* b, bool f32, const NGeom& G, hipStream_t st);
-void n_restrict(const void* r, bool f32_fine, const NGeom& Gf, void* fc, bool f32_coarse, const NGeom& Gc,
-                hipStream_t st);
 void n_prolong_add(const void* uc, bool f32_coarse, const NGeom& Gc, void* uf, bool f32_fine, const NGeom& Gf,
                    hipStream_t st);
 void n_coarse(const double* inv, const void* f, void* u, bool f32, const NGeom& G, hipStream_t st);

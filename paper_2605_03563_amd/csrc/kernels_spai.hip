@@ -4,12 +4,16 @@
 // Galerkin operator R A P), on natural-layout level arrays.
 //
 // Every operator here is a cubically symmetric 27-point stencil given by its
-// centre, face, edge and corner weights.  A thread owns one (i, j) column and
-// marches k; for each plane it forms the in-plane sums c = u(i, j),
-// f4 = the 4 in-plane face neighbours, e4 = the 4 in-plane corners, and keeps
-// them for planes k-1, k, k+1 in registers, so
-//   (S u)(i,j,k) = w_c c_k + w_f (f4_k + c_{k-1} + c_{k+1})
-//                + w_e (e4_k + f4_{k-1} + f4_{k+1}) + w_k (e4_{k-1} + e4_{k+1}).
+// centre, face, edge and corner weights.  The kernels that sweep a level
+// (smoothing step, residual norm, residual with full weighting) are marching
+// wavefronts: lane l holds a column of a few rows in registers, x-neighbours
+// come from the lanes beside by lane shifts, y-neighbours from the lane's own
+// rows, and along z only two partial sums per row are carried.  No LDS and no
+// barrier: the LDS-staged kernels before them waited at two barriers per plane
+// and spent as long on LDS reads (27 per node) as on memory.  Measured at
+// 511^3 / 255^3 / 127^3, FP64, us (before): step 804 (990) / 108 (134) / 20
+// (27), residual and full weighting 545 (1159) / 61 (147) / 13 (18), norm 387
+// (662, the rate of a plain read) / 47 (85) / 10 (12).
 #include <algorithm>
 
 #include "internal.h"
@@ -20,8 +24,7 @@ namespace {
 
 constexpr int BX = 64, BY = 4, KZ = 8;
 
-// planes per block of the 27-point kernels: 32 on the 511^3 level (2-4% less
-// time per SPAI cycle than 8: fewer plane pipelines to start), 8 from 127^3
+// planes per block of the stored residual and the prolongation
 inline int nkz(const NGeom& G) { return G.n >= 512 ? 32 : G.n >= 128 ? KZ : 1; }
 inline dim3 ngrid(const NGeom& G) {
   const int e = G.n - 1;
@@ -48,10 +51,11 @@ __device__ inline double apply_sums(const W4& w, const Plane& m, const Plane& z,
   return w.c * z.c + w.f * (z.f + m.c + p.c) + w.e * (z.e + m.f + p.f) + w.k * (m.e + p.e);
 }
 
-// r = f - A u (r stored unless r == nullptr; with NORM the squares summed
-// into one partial per block).  T is the storage type of the level (FP64, or
-// FP32 on coarse levels); all arithmetic is FP64.
-template <bool NORM, typename T>
+// r = f - A u, stored, the squares summed into one partial per block (the
+// residual operator; the cycles use k_nres_w).  A thread owns one (i, j) column
+// and keeps the in-plane sums c = u(i, j), f = the 4 in-plane face neighbours,
+// e = the 4 in-plane corners of three planes.
+template <typename T>
 __global__ __launch_bounds__(BX* BY) void k_n27(const T* __restrict__ src, const T* __restrict__ f,
                                                 T* __restrict__ dst, NGeom G, W4 w, double* __restrict__ partial) {
   int bx, by, bz;
@@ -70,166 +74,223 @@ __global__ __launch_bounds__(BX* BY) void k_n27(const T* __restrict__ src, const
       const Plane p = plane_sums(src, idx + G.P, G.W);
       const double s = apply_sums(w, m, z, p);
       const double r = (double)f[idx] - s;
-      if (dst) dst[idx] = (T)r;
-      if (NORM) acc += r * r;
+      dst[idx] = (T)r;
+      acc += r * r;
       m = z;
       z = p;
     }
   }
-  if (NORM) {
-    const double b = block_sum(acc);
-    if (threadIdx.x == 0 && threadIdx.y == 0) partial[linear_block()] = b;
-  }
+  const double b = block_sum(acc);
+  if (threadIdx.x == 0 && threadIdx.y == 0) partial[linear_block()] = b;
 }
 
-// One fused Richardson step out of place: out = u - M (f - A u) at the
-// unknowns (Eq. richardson), reading u and f once and writing out once.
-// A block owns a 64 x FY output tile and a run of planes.  Per plane q it
-// loads u on the tile plus a 2-node halo into LDS, every thread forms the
-// in-plane sums (c, f4, e4) of u for its points of the 66 x (FY+2) residual tile
-// (tile plus a 1-node halo) and keeps the last three planes of them in
-// registers, which gives r at plane q-1 (zero off the unknowns, so M acts on
-// r extended by zero); r goes to LDS, and the in-plane sums of r at the
-// thread's own column, again kept for three planes, give the output at plane
-// q-2.  Out of place because neighbouring tiles read the old u in their halos.
-constexpr int FX = 64;
-template <typename T, int FY>
-__global__ __launch_bounds__(FX* FY) void k_nspai(const T* __restrict__ u, const T* __restrict__ f,
-                                                  T* __restrict__ out, NGeom G, W4 A, W4 M) {
-  constexpr int UX = FX + 4, UY = FY + 4, RX = FX + 2, RY = FY + 2, NT = FX * FY;
-  static_assert(RX * RY <= 2 * NT, "at most two residual-tile points per thread");
-  __shared__ double Us[UY][UX];
-  __shared__ double Rs[RY][RX];
+// ---- marching wavefronts: rows in registers, x-neighbours from the lanes beside
+// The value of the lane to the left (DIR < 0) or right; the wavefront's edge
+// lane gets zero.
+template <int DIR>
+__device__ inline double lane_shift(double v) {
+  constexpr int ctrl = DIR < 0 ? 0x138 : 0x130;  // wave_shr:1, wave_shl:1
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), ctrl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), ctrl, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ inline double beside(double v) { return lane_shift<-1>(v) + lane_shift<1>(v); }
+
+// One fused Richardson step out of place: out = u - M (f - A u) at the unknowns
+// (Eq. richardson).  A wavefront owns SX = 60 columns and R rows and marches
+// the planes of its run with no LDS and no barrier: lane l holds column
+// x0 - 2 + l of R + 4 rows of u (loaded one plane ahead), forms r on 62 columns
+// and R + 2 rows and the output on 60 and R, x-neighbours by lane shifts and
+// y-neighbours from its own rows.  Along z a stencil applied to plane q is split into what
+// it gives to its own plane, a = w_c c + w_f f + w_e e, and to the two beside,
+// b = w_f c + w_e f + w_k e, so two partial sums per row are all the state.
+// Four wavefronts stacked in y share their halo rows through the cache.
+// ZG: u is zero (a coarse level's first step): it is not read.
+constexpr int SX = 60;
+template <typename T, int R, bool ZG>
+__global__ __launch_bounds__(256) void k_nspai_w(const T* __restrict__ u, const T* __restrict__ f,
+                                                 T* __restrict__ out, NGeom G, W4 A, W4 M) {
   int bx, by, bz;
   xcd_block(bx, by, bz);
-  const int n = G.n;
-  const int tid = (int)threadIdx.x + FX * (int)threadIdx.y;
-  const int i0 = 1 + bx * FX, j0 = 1 + by * FY;
+  const int n = G.n, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int gx = 1 + bx * SX - 2 + lane;
+  const int y0 = 1 + (by * 4 + wave) * R;  // first output row
   const int kz = (n - 1 + (int)gridDim.z - 1) / (int)gridDim.z;
-  const int kb = 1 + bz * kz;
-  const int ke = min(kb + kz - 1, n - 1);
-  if (kb > ke) return;  // uniform over the block
-  // residual-tile points of this thread: tid and tid + NT
-  int rx[2], ry[2];
-  bool rin[2];
-  const int np = (tid + NT < RX * RY) ? 2 : 1;
-#pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    const int idx = tid + p * NT;
-    rx[p] = idx % RX;
-    ry[p] = idx / RX;
-    const int gi = i0 - 1 + rx[p], gj = j0 - 1 + ry[p];
-    rin[p] = p < np && gi >= 1 && gi <= n - 1 && gj >= 1 && gj <= n - 1;
-  }
-  const int oi = (int)threadIdx.x, oj = (int)threadIdx.y;
-  const int gi = i0 + oi, gj = j0 + oj;
-  const bool oin = gi <= n - 1 && gj <= n - 1;
-  auto lds_sums = [](const double* b, int pitch) {
-    Plane s;
-    s.c = b[0];
-    s.f = (b[-1] + b[1]) + (b[-pitch] + b[pitch]);
-    s.e = (b[-pitch - 1] + b[-pitch + 1]) + (b[pitch - 1] + b[pitch + 1]);
-    return s;
-  };
-  Plane us[2][3] = {};
-  Plane rs[3] = {};
-  double uown[3] = {0.0, 0.0, 0.0};
-  // software pipeline: the u plane for the next iteration and the f values
-  // of the next residual plane are loaded while this plane is computed
-  constexpr int NL = (UX * UY + NT - 1) / NT;  // u-tile entries per thread (2)
-  // per-thread tile offsets, fixed over the planes
-  long long uoff[NL];
-  bool uok[NL];
-#pragma unroll
-  for (int l = 0; l < NL; ++l) {
-    const int idx = tid + l * NT;
-    const int x = idx % UX, y = idx / UX;
-    const int gx = i0 - 2 + x, gy = j0 - 2 + y;
-    uok[l] = idx < UX * UY && gx >= 0 && gx <= n && gy >= 0 && gy <= n;
-    uoff[l] = uok[l] ? (long long)gy * G.W + gx : 0;
-  }
-  long long foff[2];
-#pragma unroll
-  for (int p = 0; p < 2; ++p) foff[p] = rin[p] ? (long long)(j0 - 1 + ry[p]) * G.W + (i0 - 1 + rx[p]) : 0;
-  double ureg[NL];
+  const int kb = 1 + bz * kz, ke = min(kb + kz - 1, n - 1);
+  if (y0 > n - 1 || kb > ke) return;
+  const bool xin = gx >= 1 && gx <= n - 1;
+  const bool mine = xin && lane >= 2 && lane < 2 + SX;
+  const int cx = min(max(gx, 0), n);  // loads stay in the array
+  const bool ux = gx >= 0 && gx <= n;
+  double un[R + 4], fn[R + 2];         // the next plane's rows
   auto load_u = [&](int q) {
-    const bool qok = q >= 0 && q <= n;
-    const long long base = (long long)q * G.P;
+    if (ZG) return;
+    const T* p = u + (long long)min(max(q, 0), n) * G.P + cx;
 #pragma unroll
-    for (int l = 0; l < NL; ++l) ureg[l] = (qok && uok[l]) ? (double)u[base + uoff[l]] : 0.0;
+    for (int i = 0; i < R + 4; ++i) un[i] = (double)p[(long long)min(max(y0 - 2 + i, 0), n) * G.W];
   };
-  double freg[2] = {0.0, 0.0};
-  auto load_f = [&](int pr) {
-    const bool pok = pr >= 1 && pr <= n - 1;
-    const long long base = (long long)pr * G.P;
+  auto load_f = [&](int q) {
+    const T* p = f + (long long)min(max(q, 1), n - 1) * G.P + cx;
 #pragma unroll
-    for (int p = 0; p < 2; ++p) freg[p] = (pok && rin[p]) ? (double)f[base + foff[p]] : 0.0;
+    for (int i = 0; i < R + 2; ++i) fn[i] = (double)p[(long long)min(max(y0 - 1 + i, 1), n - 1) * G.W];
   };
+  double rp[R + 2], rb[R + 2];  // r: sum so far for the plane before, its b
+  double op[R], ob[R], u1[R], u2[R];
+#pragma unroll
+  for (int i = 0; i < R + 2; ++i) rp[i] = rb[i] = 0.0;
+#pragma unroll
+  for (int i = 0; i < R; ++i) op[i] = ob[i] = u1[i] = u2[i] = 0.0;
   load_u(kb - 2);
   load_f(kb - 1);
   for (int q = kb - 2; q <= ke + 2; ++q) {
+    double c[R + 4], h[R + 4];
+    const bool qin = q >= 0 && q <= n;
 #pragma unroll
-    for (int l = 0; l < NL; ++l) {
-      const int idx = tid + l * NT;
-      if (idx < UX * UY) (&Us[0][0])[idx] = ureg[l];
+    for (int i = 0; i < R + 4; ++i) {
+      const int y = y0 - 2 + i;
+      c[i] = !ZG && qin && y >= 0 && y <= n && ux ? un[i] : 0.0;
     }
-    __syncthreads();
-    if (q + 1 <= ke + 2) load_u(q + 1);
-    const double fcur0 = freg[0], fcur1 = freg[1];
-    if (q >= kb && q <= ke + 1) load_f(q);
-    uown[0] = uown[1];
-    uown[1] = uown[2];
-    uown[2] = Us[oj + 2][oi + 2];
+    double fc[R + 2];
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      if (p < np) {
-        us[p][0] = us[p][1];
-        us[p][1] = us[p][2];
-        us[p][2] = lds_sums(&Us[ry[p] + 1][rx[p] + 1], UX);
-        if (q >= kb) {
-          const int pr = q - 1;
-          double r = 0.0;
-          if (rin[p] && pr >= 1 && pr <= n - 1)
-            r = (p == 0 ? fcur0 : fcur1) - apply_sums(A, us[p][0], us[p][1], us[p][2]);
-          Rs[ry[p]][rx[p]] = r;
+    for (int i = 0; i < R + 2; ++i) fc[i] = fn[i];
+    if (q < ke + 2) load_u(q + 1);
+    if (q >= kb && q <= ke + 1) load_f(q);
+#pragma unroll
+    for (int i = 0; i < R + 4; ++i) h[i] = ZG ? 0.0 : beside(c[i]);
+    // r on plane q - 1
+    double r[R + 2];
+    const bool rin = q - 1 >= 1 && q - 1 <= n - 1;
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+      const double fs = h[i + 1] + (c[i] + c[i + 2]), es = h[i] + h[i + 2];
+      const double b = A.f * c[i + 1] + A.e * fs + A.k * es;
+      const int y = y0 - 1 + i;
+      r[i] = rin && xin && y >= 1 && y <= n - 1 ? fc[i] - (rp[i] + b) : 0.0;
+      rp[i] = A.c * c[i + 1] + A.f * fs + A.e * es + rb[i];
+      rb[i] = b;
+    }
+    double g[R + 2];
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) g[i] = beside(r[i]);
+    // output on plane q - 2
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const double fs = g[i + 1] + (r[i] + r[i + 2]), es = g[i] + g[i + 2];
+      const double b = M.f * r[i + 1] + M.e * fs + M.k * es;
+      const int y = y0 + i;
+      if (q >= kb + 2 && mine && y <= n - 1)
+        __builtin_nontemporal_store((T)(u2[i] - (op[i] + b)), out + G.at(gx, y, q - 2));
+      op[i] = M.c * r[i + 1] + M.f * fs + M.e * es + ob[i];
+      ob[i] = b;
+      u2[i] = u1[i];
+      u1[i] = c[i + 2];
+    }
+  }
+}
+
+// r = f - A u, marching as k_nspai_w: R rows and 62 columns of r per wavefront.
+// NORM: one partial sum of r^2 per block.  Otherwise the residual is fully
+// weighted onto the coarse grid without being stored (Gf.n even, R odd: the
+// fine rows 2 J0 - 1 .. 2 J0 + R - 2 of (R - 1) / 2 coarse rows; 30 coarse columns on the even
+// fine ones): weights 1, 2, 1 along each axis, over 64.
+template <typename T, typename TC, int R, bool NORM>
+__global__ __launch_bounds__(256) void k_nres_w(const T* __restrict__ u, const T* __restrict__ f, NGeom G, W4 A,
+                                                TC* __restrict__ fc, NGeom Gc, double* __restrict__ partial) {
+  constexpr int RC = (R - 1) / 2;          // coarse rows per wavefront
+  constexpr int RX = NORM ? 62 : 60;       // columns a wavefront advances
+  constexpr int RY = NORM ? R : R - 1;     // rows
+  int bx, by, bz;
+  xcd_block(bx, by, bz);
+  const int n = G.n, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int gx = bx * RX + lane;                 // lanes 1 .. 62 hold r
+  const int y0 = 1 + (by * 4 + wave) * RY;       // first row of r
+  const int runs = (int)gridDim.z;
+  // planes of r: kb .. ke (restriction: from an odd plane to an odd plane)
+  int kb, ke;
+  if (NORM) {
+    const int kz = (n - 1 + runs - 1) / runs;
+    kb = 1 + bz * kz;
+    ke = min(kb + kz - 1, n - 1);
+  } else {
+    const int kz = (Gc.n - 1 + runs - 1) / runs, K0 = 1 + bz * kz;
+    kb = 2 * K0 - 1;
+    ke = 2 * min(K0 + kz - 1, Gc.n - 1) + 1;
+  }
+  const bool work = y0 <= n - 1 && kb <= ke;
+  double acc = 0.0;
+  if (work) {
+    const bool xin = gx >= 1 && gx <= n - 1 && lane >= 1 && lane <= 62;
+    const int cx = min(gx, n);
+    double un[R + 2], fn[R];
+    auto load_u = [&](int q) {
+      const T* p = u + (long long)min(q, n) * G.P + cx;
+#pragma unroll
+      for (int i = 0; i < R + 2; ++i) un[i] = (double)p[(long long)min(y0 - 1 + i, n) * G.W];
+    };
+    auto load_f = [&](int q) {
+      const T* p = f + (long long)min(max(q, 1), n - 1) * G.P + cx;
+#pragma unroll
+      for (int i = 0; i < R; ++i) fn[i] = (double)p[(long long)min(y0 + i, n - 1) * G.W];
+    };
+    double rp[R], rb[R], z0[RC > 0 ? RC : 1];
+#pragma unroll
+    for (int i = 0; i < R; ++i) rp[i] = rb[i] = 0.0;
+#pragma unroll
+    for (int i = 0; i < RC; ++i) z0[i] = 0.0;
+    load_u(kb - 1);
+    load_f(kb);
+    // plane q of u completes r on plane q - 1
+    for (int q = kb - 1; q <= ke + 1; ++q) {
+      double c[R + 2], h[R + 2], fr[R];
+#pragma unroll
+      for (int i = 0; i < R + 2; ++i) c[i] = gx <= n && y0 - 1 + i <= n ? un[i] : 0.0;
+#pragma unroll
+      for (int i = 0; i < R; ++i) fr[i] = fn[i];
+      if (q <= ke) load_u(q + 1);
+      if (q > kb && q <= ke) load_f(q);
+#pragma unroll
+      for (int i = 0; i < R + 2; ++i) h[i] = beside(c[i]);
+      const int k = q - 1;
+      double r[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const double fs = h[i + 1] + (c[i] + c[i + 2]), es = h[i] + h[i + 2];
+        const double b = A.f * c[i + 1] + A.e * fs + A.k * es;
+        r[i] = xin && y0 + i <= n - 1 && k >= kb && k <= n - 1 ? fr[i] - (rp[i] + b) : 0.0;
+        if (NORM && k >= kb) acc += r[i] * r[i];
+        rp[i] = A.c * c[i + 1] + A.f * fs + A.e * es + rb[i];
+        rb[i] = b;
+      }
+      if constexpr (!NORM) {
+        double x[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) x[i] = 2.0 * r[i] + beside(r[i]);
+#pragma unroll
+        for (int i = 0; i < RC; ++i) {
+          const double p = x[2 * i] + 2.0 * x[2 * i + 1] + x[2 * i + 2];
+          if (k & 1) {  // closes coarse plane (k - 1) / 2 and opens the next
+            const int J = (y0 + 1) / 2 + i, I = gx >> 1;
+            if (k > kb && !(gx & 1) && lane >= 2 && lane <= 60 && I >= 1 && I < Gc.n && J < Gc.n)
+              fc[Gc.at(I, J, (k - 1) >> 1)] = (TC)((z0[i] + p) * (1.0 / 64.0));
+            z0[i] = p;
+          } else {
+            z0[i] += 2.0 * p;
+          }
         }
       }
     }
-    __syncthreads();
-    if (q >= kb) {
-      rs[0] = rs[1];
-      rs[1] = rs[2];
-      rs[2] = lds_sums(&Rs[oj + 1][oi + 1], RX);
-      if (q >= kb + 2 && oin)
-        __builtin_nontemporal_store((T)(uown[0] - apply_sums(M, rs[0], rs[1], rs[2])), out + G.at(gi, gj, q - 2));
-    }
+  }
+  if constexpr (NORM) {
+    const double s = block_sum(acc);
+    if (threadIdx.x == 0) partial[linear_block()] = s;
   }
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_ncopy(const T* __restrict__ a, T* __restrict__ b, long long count) {
   for (long long i = blockIdx.x * 256LL + threadIdx.x; i < count; i += (long long)gridDim.x * 256) b[i] = a[i];
-}
-
-// coarse f(I,J,K) = full weighting of the fine residual around (2I,2J,2K)
-template <typename TF, typename TC>
-__global__ __launch_bounds__(BX* BY) void k_nrestrict(const TF* __restrict__ r, NGeom Gf, TC* __restrict__ fc,
-                                                      NGeom Gc) {
-  int bx, by, bz;
-  xcd_block(bx, by, bz);
-  const int I = 1 + bx * BX + (int)threadIdx.x;
-  const int J = 1 + by * BY + (int)threadIdx.y;
-  const int K = 1 + bz;
-  if (I >= Gc.n || J >= Gc.n || K >= Gc.n) return;
-  const long long c = Gf.at(2 * I, 2 * J, 2 * K);
-  auto v = [&](long long q) { return (double)r[q]; };
-  auto plane = [&](long long q) {
-    const double a = v(q - 1) + 2.0 * v(q) + v(q + 1);
-    const double b = v(q - Gf.W - 1) + 2.0 * v(q - Gf.W) + v(q - Gf.W + 1);
-    const double d = v(q + Gf.W - 1) + 2.0 * v(q + Gf.W) + v(q + Gf.W + 1);
-    return b + 2.0 * a + d;
-  };
-  fc[Gc.at(I, J, K)] = (TC)((plane(c - Gf.P) + 2.0 * plane(c) + plane(c + Gf.P)) * (1.0 / 64.0));
 }
 
 // fine u += trilinear interpolation of the coarse correction (P = 8 R^T).
@@ -438,41 +499,41 @@ long long n27_blocks(const NGeom& G) {
   return (long long)g.x * g.y * g.z;
 }
 
-void n27_residual(const void* u, const void* f, void* r, bool f32, const NGeom& G, const W4& A, bool norm,
-                  double* partial, hipStream_t st) {
-  const dim3 gr = ngrid(G), bl(BX, BY);
-  if (f32) {
-    if (norm)
-      k_n27<true, float><<<gr, bl, 0, st>>>((const float*)u, (const float*)f, (float*)r, G, A, partial);
-    else
-      k_n27<false, float><<<gr, bl, 0, st>>>((const float*)u, (const float*)f, (float*)r, G, A, nullptr);
-  } else {
-    if (norm)
-      k_n27<true, double><<<gr, bl, 0, st>>>((const double*)u, (const double*)f, (double*)r, G, A, partial);
-    else
-      k_n27<false, double><<<gr, bl, 0, st>>>((const double*)u, (const double*)f, (double*)r, G, A, nullptr);
-  }
+void n27_residual(const double* u, const double* f, double* r, const NGeom& G, const W4& A, double* partial,
+                  hipStream_t st) {
+  k_n27<double><<<ngrid(G), dim3(BX, BY), 0, st>>>(u, f, r, G, A, partial);
 }
 
-// Tile rows FY and planes per block kz: on the 511^3 level 64 x 16 tiles
-// and runs of 128 planes (1024 blocks of 1024 threads) take 0.98 ms per
-// step against 1.11 ms with 64 x 8 tiles and 32 planes (less recomputed
-// halo, fewer pipeline start-ups); smaller levels keep 64 x 8 and shorter
-// runs so that they still spread over the compute units.
-template <int FY>
-inline dim3 fgrid(const NGeom& G, int kz) {
+// Rows per wavefront R and planes per run kz of the marching kernels: more
+// rows share more of a row's loads, fewer and shorter runs give a small level
+// enough wavefronts.  Step at 127^3 20 us with (R, kz) = (4, 4), 23 with (2, 4), 29
+// with (4, 16); at 255^3 108 with (4, 16), 125 with (4, 4), 125 with (2, 16);
+// at 511^3 804 with (4, 32), 888 with (2, 32), 956 with (4, 256); at 31^3 5.8
+// with (2, 1), 7.8 with (2, 4); at 63^3 8.2 with (2, 4), 11 with (2, 1).
+struct March {
+  int R, kz;
+};
+static March step_march(int n) {
+  return n < 48 ? March{2, 1} : n < 96 ? March{2, 4} : n < 160 ? March{4, 4} : n < 384 ? March{4, 16} : March{4, 32};
+}
+
+template <typename T, int R>
+static void spai_step_go(const T* u, const T* f, T* out, const NGeom& G, const W4& A, const W4& M, int kz,
+                         hipStream_t st) {
   const int e = G.n - 1;
-  return dim3((e + FX - 1) / FX, (e + FY - 1) / FY, (e + kz - 1) / kz);
+  const dim3 gr((e + SX - 1) / SX, (e + 4 * R - 1) / (4 * R), (e + kz - 1) / kz);
+  if (u)
+    k_nspai_w<T, R, false><<<gr, 256, 0, st>>>(u, f, out, G, A, M);
+  else
+    k_nspai_w<T, R, true><<<gr, 256, 0, st>>>(u, f, out, G, A, M);
 }
-
 template <typename T>
 static void spai_step_t(const T* u, const T* f, T* out, const NGeom& G, const W4& A, const W4& M, hipStream_t st) {
-  if (G.n >= 512) {
-    k_nspai<T, 16><<<fgrid<16>(G, 128), dim3(FX, 16), 0, st>>>(u, f, out, G, A, M);
-  } else {
-    const int kz = G.n >= 256 ? 32 : G.n >= 128 ? 16 : 4;
-    k_nspai<T, 8><<<fgrid<8>(G, kz), dim3(FX, 8), 0, st>>>(u, f, out, G, A, M);
-  }
+  const March m = step_march(G.n);
+  if (m.R == 2)
+    spai_step_go<T, 2>(u, f, out, G, A, M, m.kz, st);
+  else
+    spai_step_go<T, 4>(u, f, out, G, A, M, m.kz, st);
 }
 
 void n_spai_step(const void* u, const void* f, void* out, bool f32, const NGeom& G, const W4& A, const W4& M,
@@ -483,6 +544,47 @@ void n_spai_step(const void* u, const void* f, void* out, bool f32, const NGeom&
     spai_step_t<double>((const double*)u, (const double*)f, (double*)out, G, A, M, st);
 }
 
+// As the step's rule: norm at 63^3 4.7 us with (4, 2), 5.2 with (4, 1); at 127^3 9.8
+// with (4, 4), 11.7 with (4, 2); at 255^3 47 with (4, 16), 52 with (4, 4).
+static March norm_march(int n) {
+  return n < 48 ? March{2, 1} : n < 96 ? March{4, 2} : n < 160 ? March{4, 4} : n < 384 ? March{4, 16} : March{4, 32};
+}
+int n27_norm(const double* u, const double* f, const NGeom& G, const W4& A, double* partial, hipStream_t st) {
+  const March m = norm_march(G.n);
+  const int e = G.n - 1;
+  const dim3 gr((e + 61) / 62, (e + 4 * m.R - 1) / (4 * m.R), (e + m.kz - 1) / m.kz);
+  if (m.R == 2)
+    k_nres_w<double, double, 2, true><<<gr, 256, 0, st>>>(u, f, G, A, nullptr, G, partial);
+  else
+    k_nres_w<double, double, 4, true><<<gr, 256, 0, st>>>(u, f, G, A, nullptr, G, partial);
+  return (int)(gr.x * gr.y * gr.z);
+}
+
+// Rows of r (2 or 4 fine rows advance, R - 1) and coarse planes per run: 4.5 us at
+// 31^3 with (3, 1), 5.3 with (5, 1); at 127^3 12.6 with (5, 2), 14.0 with (3,
+// 4); at 255^3 61 with (5, 8), 69 with (5, 16); at 511^3 545 with (5, 16), 578 with (5, 2).
+template <typename T, typename TC>
+static void resrestrict_t(const T* u, const T* f, const NGeom& G, const W4& A, TC* fc, const NGeom& Gc,
+                          hipStream_t st) {
+  const March m = G.n < 96 ? March{3, 1} : G.n < 160 ? March{5, 2} : G.n < 384 ? March{5, 8} : March{5, 16};
+  const int e = Gc.n - 1, rc = (m.R - 1) / 2;
+  const dim3 gr((e + 29) / 30, (e + 4 * rc - 1) / (4 * rc), (e + m.kz - 1) / m.kz);
+  if (m.R == 3)
+    k_nres_w<T, TC, 3, false><<<gr, 256, 0, st>>>(u, f, G, A, fc, Gc, nullptr);
+  else
+    k_nres_w<T, TC, 5, false><<<gr, 256, 0, st>>>(u, f, G, A, fc, Gc, nullptr);
+}
+
+void n_resrestrict(const void* u, const void* f, bool f32, const NGeom& G, const W4& A, void* fc, bool f32_coarse,
+                   const NGeom& Gc, hipStream_t st) {
+  if (f32)  // the levels below an FP32 level are FP32
+    resrestrict_t((const float*)u, (const float*)f, G, A, (float*)fc, Gc, st);
+  else if (f32_coarse)
+    resrestrict_t((const double*)u, (const double*)f, G, A, (float*)fc, Gc, st);
+  else
+    resrestrict_t((const double*)u, (const double*)f, G, A, (double*)fc, Gc, st);
+}
+
 void n_copy(const void* a, void* b, bool f32, const NGeom& G, hipStream_t st) {
   const long long count = G.total();
   const long long blocks = std::min<long long>((count + 255) / 256, 65536);
@@ -490,19 +592,6 @@ void n_copy(const void* a, void* b, bool f32, const NGeom& G, hipStream_t st) {
     k_ncopy<float><<<(unsigned)blocks, 256, 0, st>>>((const float*)a, (float*)b, count);
   else
     k_ncopy<double><<<(unsigned)blocks, 256, 0, st>>>((const double*)a, (double*)b, count);
-}
-
-void n_restrict(const void* r, bool f32_fine, const NGeom& Gf, void* fc, bool f32_coarse, const NGeom& Gc,
-                hipStream_t st) {
-  const dim3 gr = inner_grid(Gc), bl(BX, BY);
-  if (f32_fine && f32_coarse)
-    k_nrestrict<float, float><<<gr, bl, 0, st>>>((const float*)r, Gf, (float*)fc, Gc);
-  else if (!f32_fine && f32_coarse)
-    k_nrestrict<double, float><<<gr, bl, 0, st>>>((const double*)r, Gf, (float*)fc, Gc);
-  else if (!f32_fine && !f32_coarse)
-    k_nrestrict<double, double><<<gr, bl, 0, st>>>((const double*)r, Gf, (double*)fc, Gc);
-  else
-    k_nrestrict<float, double><<<gr, bl, 0, st>>>((const float*)r, Gf, (double*)fc, Gc);
 }
 
 void n_prolong_add(const void* uc, bool f32_coarse, const NGeom& Gc, void* uf, bool f32_fine, const NGeom& Gf,

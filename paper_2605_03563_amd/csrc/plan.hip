@@ -500,7 +500,7 @@ void carve(poisson_plan_s* P, Carver& cv) {
       L.u = cv.take(b);
       L.u2 = dense_only ? nullptr : cv.take(b);
       L.f = cv.take(b);
-      L.r = dense_only ? nullptr : cv.take(b);
+      L.r = nl == n ? cv.take(b) : nullptr;  // the residual operator's result
       P->nlv.push_back(L);
       if (nl == o.coarsest) break;
     }
@@ -981,19 +981,21 @@ int capture_sph_iteration(poisson_plan_s* P, double* phi) {
 }
 
 // `steps` fused Richardson steps on level L, alternating between u and u2;
-// returns the array holding the result.
-void* spai_smooth(NLevel& L, void* cur, int steps, hipStream_t st) {
+// returns the array holding the result.  zero: the first step takes the
+// unknowns as zero.
+void* spai_smooth(NLevel& L, void* cur, int steps, hipStream_t st, bool zero = false) {
   for (int s = 0; s < steps; ++s) {
     void* nxt = (cur == L.u) ? L.u2 : L.u;
-    n_spai_step(cur, L.f, nxt, L.f32, L.G, L.A, L.M, st);
+    n_spai_step(zero && s == 0 ? nullptr : cur, L.f, nxt, L.f32, L.G, L.A, L.M, st);
     cur = nxt;
   }
   return cur;
 }
 
 // One SPAI V(nu1, nu2) cycle from level l: Richardson steps u <- u - M (f - A u)
-// (Eq. richardson), Galerkin coarse problems on a zero initial guess.  The
-// result is left in L.u (copied back when the step count is odd).
+// (Eq. richardson), Galerkin coarse problems on a zero initial guess (the
+// first step of a coarse level does not read it).  The result is left in L.u
+// (copied back when the step count is odd).
 void spai_vcycle(poisson_plan_s* P, int l, hipStream_t st) {
   NLevel& L = P->nlv[l];
   if (l + 1 == (int)P->nlv.size()) {
@@ -1003,11 +1005,10 @@ void spai_vcycle(poisson_plan_s* P, int l, hipStream_t st) {
       n_coarse(P->cinv, L.f, L.u, L.f32, L.G, st);
     return;
   }
-  void* cur = spai_smooth(L, L.u, P->opts.nu1, st);
-  n27_residual(cur, L.f, L.r, L.f32, L.G, L.A, false, nullptr, st);
+  if (l > 0 && P->opts.nu1 == 0) fill_zero(L.u, L.f32, L.G.total(), st);
+  void* cur = spai_smooth(L, L.u, P->opts.nu1, st, l > 0);
   NLevel& C = P->nlv[l + 1];
-  n_restrict(L.r, L.f32, L.G, C.f, C.f32, C.G, st);
-  fill_zero(C.u, C.f32, C.G.total(), st);
+  n_resrestrict(cur, L.f, L.f32, L.G, L.A, C.f, C.f32, C.G, st);
   spai_vcycle(P, l + 1, st);
   n_prolong_add(C.u, C.f32, C.G, cur, L.f32, L.G, st);
   cur = spai_smooth(L, cur, P->opts.nu2, st);
@@ -1017,8 +1018,8 @@ void spai_vcycle(poisson_plan_s* P, int l, hipStream_t st) {
 void spai_step(poisson_plan_s* P, hipStream_t st, const Post& post) {
   NLevel& L = P->nlv[0];
   spai_vcycle(P, 0, st);
-  n27_residual(L.u, L.f, nullptr, false, L.G, L.A, true, P->partial, st);
-  finish_sum(P->partial, (int)n27_blocks(L.G), 1, P->scal, kRes2, st, post);
+  const int nb = n27_norm((const double*)L.u, (const double*)L.f, L.G, L.A, P->partial, st);
+  finish_sum(P->partial, nb, 1, P->scal, kRes2, st, post);
 }
 
 // One multigrid iteration followed by the fine residual norm into
@@ -1313,17 +1314,17 @@ int solve_spai(poisson_plan_s* P, const double* rho, double* phi, double tol, po
   Tracker T{stats};
   if (stats) stats->history_len = 0;
   NLevel& L = P->nlv[0];
-  const int nb = (int)n27_blocks(L.G);
   HIPCHK(hipEventRecord(P->ev[0], st));
   if (o.lmax >= 0) CHK(do_multipole(P, rho, phi, o.lmax, nullptr));
   HIPCHK(hipEventRecord(P->ev[1], st));
   n_rhs(rho, g.pitch[0], g.pitch[1], g.ghost, (double*)L.f, L.G, o.order, o.four_pi_G, st);
   n_from_caller(phi, g.pitch[0], g.pitch[1], g.ghost, (double*)L.u, L.G, true, st);
-  n27_residual(L.u, L.f, nullptr, false, L.G, L.A, true, P->partial, st);
+  const double *u = (const double*)L.u, *f = (const double*)L.f;
+  int nb = n27_norm(u, f, L.G, L.A, P->partial, st);
   finish_sum(P->partial, nb, 1, P->scal, kBnorm2, st);
   n_from_caller(phi, g.pitch[0], g.pitch[1], g.ghost, (double*)L.u, L.G, false, st);
   if (L.u2) n_from_caller(phi, g.pitch[0], g.pitch[1], g.ghost, (double*)L.u2, L.G, false, st);
-  n27_residual(L.u, L.f, nullptr, false, L.G, L.A, true, P->partial, st);
+  nb = n27_norm(u, f, L.G, L.A, P->partial, st);
   finish_sum(P->partial, nb, 1, P->scal, kRes2, st, first_post(P));
   CHK(launch_check("SPAI setup"));
   CHK(wait_post(P, P->posted, 2));
@@ -2144,7 +2145,7 @@ int poisson_op_residual(poisson_plan_t P, const double* d_rho, const double* d_p
     NLevel& L = P->nlv[0];
     n_rhs(d_rho, g.pitch[0], g.pitch[1], g.ghost, (double*)L.f, L.G, P->order, P->opts.four_pi_G, st);
     n_from_caller(d_phi, g.pitch[0], g.pitch[1], g.ghost, (double*)L.u, L.G, false, st);
-    n27_residual(L.u, L.f, L.r, false, L.G, L.A, true, P->partial, st);
+    n27_residual((const double*)L.u, (const double*)L.f, (double*)L.r, L.G, L.A, P->partial, st);
     finish_sum(P->partial, (int)n27_blocks(L.G), 1, P->scal, kRes2, st);
     n_to_caller((const double*)L.r, L.G, d_res, g.pitch[0], g.pitch[1], g.ghost, st);
   } else {
