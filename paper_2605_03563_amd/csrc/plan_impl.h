@@ -50,6 +50,7 @@ struct poisson_plan_s {
   bool mg32 = false;
   double* cinv = nullptr;
   int ncoarse = 0;
+  bool fresh = true;  // the finest potential has not been swept since it was set
   // levels tail .. run in one workgroup (-1: none fit, and cinv serves the
   // coarsest level); its arguments and the coarsest inverse's blocks
   int tail = -1;
