@@ -372,6 +372,133 @@ __global__ __launch_bounds__(1024) void k_sline(SLev L, int colour, int zero_gue
     L.u[L.at(a, j, k0 + q)] = Y[(size_t)q * nt + t] - (xl * v[q] + xr * w[q]);
 }
 
+// The same pass with the split fixed at compile time (SL nodes per segment, P
+// segments).  It is bound by latency: one round of workgroups fills the chip,
+// so a pass takes as long as one thread's chain.  The segment therefore stays
+// in registers (with a runtime split Y went through LDS three times), the 5 SL
+// loads are all underway before the recurrences begin, and the interface
+// system is read from LDS.  The blocks of neighbouring colatitudes share an
+// XCD's L2, since each reads the other's lines.  TAB1: one table per
+// colatitude (log grid), read through the scalar cache.
+// Per pass, against the runtime split: 256 x 128 x 256 16.7 us (31.3; 23.8
+// without the XCD order), 128 x 64 x 128 7.1 (15.5), 64 x 32 x 64 5.0 (9.7),
+// 32 x 16 x 32 4.5 (7.5), 16 x 8 x 16 4.1 (6.3).
+template <int SL, int P, bool TAB1>
+__global__ __launch_bounds__(1024) void k_sline_t(SLev L, int nls, int colour, int zero_guess) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  constexpr int N2 = 2 * P;
+  const int nl = 1 << nls, t = threadIdx.x;
+  const int line = t & (nl - 1), sgi = t >> nls;
+  int bx, j, bz;
+  xcd_block(bx, j, bz);
+  const int par = (j + colour) & 1;
+  if (par >= L.nr) return;
+  const int i = 2 * (bx * nl + line) + par;
+  float* Gs = lds;              // interface inverse (TAB1)
+  float* E = lds + (TAB1 ? N2 * N2 : 0);
+  const float* tb = L.ltab + ((size_t)(TAB1 ? 0 : min(i, L.ntab - 1)) * L.nth + j) * L.tstride;
+  const float* G = tb + 4 * SL;
+  if constexpr (TAB1)
+    for (int q = t; q < N2 * N2; q += nl * P) Gs[q] = G[q];
+  const bool act = i < L.nr;
+  const float aphi = L.isin2[j] * L.idp2;
+  const int half = L.nph >> 1, k0 = sgi * SL, p1 = (int)L.p1;
+  const int a = min(i, L.nr - 1 - ((L.nr - 1 - par) & 1)) + 1;  // idle lanes load an own-colour line
+  // a is odd for even i: its radial neighbours lie in the other half of the row
+  const int right = par ? L.hp : 1 - L.hp, left = par ? L.hp - 1 : -L.hp;
+  const int o = (int)L.at(a, j, k0);
+  float y[SL];
+#pragma unroll
+  for (int q = 0; q < SL; ++q) y[q] = L.f[o + q * p1];
+  if (zero_guess != 1) {
+    const float cr = L.rcr[a - 1], cl = L.rcl[a - 1];
+    const float cjp = L.idt2 + L.cot2[j], cjm = L.idt2 - L.cot2[j];
+    float ur[SL], ul[SL], up[SL], um[SL];
+#pragma unroll
+    for (int q = 0; q < SL; ++q) {
+      const float* u = L.u + o + q * p1;
+      ur[q] = u[right];
+      ul[q] = u[left];
+      // across a pole: the line itself half a turn away (still zero in the
+      // first sweep of a cycle)
+      const bool top = j + 1 == L.nth, bottom = j == 0;
+      float pole = 0.0f;
+      if ((top || bottom) && zero_guess != 2) {
+        const int k = k0 + q + half;
+        pole = L.u[o + ((k >= L.nph ? k - L.nph : k) - k0) * p1];
+      }
+      up[q] = top ? pole : u[L.p0];
+      um[q] = bottom ? pole : u[-L.p0];
+    }
+#pragma unroll
+    for (int q = 0; q < SL; ++q) y[q] -= cr * ur[q] + cl * ul[q] + cjp * up[q] + cjm * um[q];
+  }
+  float d = 0.0f;
+#pragma unroll
+  for (int q = 0; q < SL; ++q) {
+    d = (y[q] - aphi * d) * tb[q];
+    y[q] = d;
+  }
+#pragma unroll
+  for (int q = SL - 2; q >= 0; --q) y[q] -= tb[SL + q] * y[q + 1];
+  E[(2 * sgi) * nl + line] = y[0];
+  E[(2 * sgi + 1) * nl + line] = y[SL - 1];
+  __syncthreads();
+  if (!act) return;
+  const int rl = 2 * (sgi == 0 ? P - 1 : sgi - 1) + 1, rr = 2 * (sgi == P - 1 ? 0 : sgi + 1);
+  const float* gl = (TAB1 ? Gs : G) + rl * N2;
+  const float* gr = (TAB1 ? Gs : G) + rr * N2;
+  float xl = 0.0f, xr = 0.0f;
+#pragma unroll
+  for (int q = 0; q < N2; ++q) {
+    const float e = E[q * nl + line];
+    xl += gl[q] * e;
+    xr += gr[q] * e;
+  }
+  xl *= aphi;
+  xr *= aphi;
+#pragma unroll
+  for (int q = 0; q < SL; ++q) L.u[o + q * p1] = y[q] - (xl * tb[2 * SL + q] + xr * tb[3 * SL + q]);
+}
+
+template <int SL, int P>
+void sline_go(const SLev& L, int colour, int zero_guess, hipStream_t st) {
+  const int lines = (L.nr + 1) / 2;
+  // lines per block: the most that leave a block for every CU, down to 16 (64-
+  // byte rows): 128 x 64 x 128 takes 7.1 us with 16 lines, 7.8 with 64; at 256 x
+  // 128 x 256 16.7 with 32, 19.1 with 16
+  int nls = 6;
+  while (nls > 4 && ((P << nls) > 512 || (long long)(((lines - 1) >> nls) + 1) * L.nth < 256)) --nls;
+  const int nl = 1 << nls;
+  const dim3 grid((lines + nl - 1) >> nls, L.nth);
+  const size_t lds = sizeof(float) * ((size_t)2 * P * nl + (L.ntab == 1 ? 4 * P * P : 0));
+  if (L.ntab == 1)
+    k_sline_t<SL, P, true><<<grid, nl * P, lds, st>>>(L, nls, colour, zero_guess);
+  else
+    k_sline_t<SL, P, false><<<grid, nl * P, lds, st>>>(L, nls, colour, zero_guess);
+}
+
+// The splits that line_split makes of the sizes 2^m and 3 2^m in use: 64 x 32 x
+// 64 takes 5.0 us here, 9.7 with the runtime split, which takes the others.
+bool sline_fixed(const SLev& L, int colour, int zero_guess, hipStream_t st) {
+  if (L.count() >= (1ll << 31)) return false;
+  if (L.nseg == 8 && L.seg == 2) {
+    sline_go<2, 8>(L, colour, zero_guess, st);
+    return true;
+  }
+  if (L.nseg != 16) return false;
+  switch (L.seg) {
+    case 2: sline_go<2, 16>(L, colour, zero_guess, st); return true;
+    case 3: sline_go<3, 16>(L, colour, zero_guess, st); return true;
+    case 4: sline_go<4, 16>(L, colour, zero_guess, st); return true;
+    case 6: sline_go<6, 16>(L, colour, zero_guess, st); return true;
+    case 8: sline_go<8, 16>(L, colour, zero_guess, st); return true;
+    case 12: sline_go<12, 16>(L, colour, zero_guess, st); return true;
+    case 16: sline_go<16, 16>(L, colour, zero_guess, st); return true;
+    default: return false;
+  }
+}
+
 // Thread x of a level row takes radial array index a in the row's storage
 // order (even a first, then odd), so a wavefront's accesses are contiguous;
 // returns the unknown index a - 1 (outside 0 .. nr-1 for ghosts and padding).
@@ -519,6 +646,7 @@ void bicg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipSt
 }
 
 void sph_line_pass(const SLev& L, int colour, int zero_guess, hipStream_t st) {
+  if (sline_fixed(L, colour, zero_guess, st)) return;
   const int nt = L.nl * L.nseg;
   const size_t lds = sizeof(float) * ((size_t)L.seg * nt + (size_t)2 * L.nseg * L.nl);
   const int lines = (L.nr + 1) / 2;
