@@ -85,7 +85,7 @@ struct SLev {
   float idt2, idp2;
   float* u;
   float* f;
-  float* r;
+  float* u2;           // a second solution array (finest level)
   const float* rcl;    // per radial unknown i
   const float* rcr;
   const float* cot2;   // cot(theta_j) / (2 dtheta)
@@ -342,15 +342,21 @@ void pbicg_direction(const double* r, double* p, const double* v, double* phat, 
                      const SphCoef& c, const Scalars* scal, hipStream_t st);
 void pbicg_s(const double* r, const double* v, double* s, double* shat, const SGeom& S, const SphCoef& c,
              const Scalars* scal, hipStream_t st);
-// the same vector updates without the Gauss-Seidel preconditioner
+// the same vector updates for the multigrid preconditioner: p (s) also goes to
+// L0.f in FP32
 void pbicg_update_p(const double* r, double* p, const double* v, const SGeom& S, const SphCoef& c,
-                    const Scalars* scal, hipStream_t st);
+                    const Scalars* scal, const SLev& L0, hipStream_t st);
 void pbicg_update_s(const double* r, const double* v, double* s, const SGeom& S, const SphCoef& c,
-                    const Scalars* scal, hipStream_t st);
+                    const Scalars* scal, const SLev& L0, hipStream_t st);
+// (32: xhat, phat and shat are the u of FP32 levels)
 void pbicg_apply(const double* xhat, double* out, const double* w, int mode, const SGeom& S,
                  const SphCoef& c, double* partial, hipStream_t st);
+void pbicg_apply32(const SLev& xhat, double* out, const double* w, int mode, const SGeom& S,
+                   const SphCoef& c, double* partial, hipStream_t st);
 void pbicg_xr(double* x, double* r, const double* phat, const double* shat, const double* s, const double* t,
               const double* rhat, const SGeom& S, const Scalars* scal, double* partial, hipStream_t st);
+void pbicg_xr32(double* x, double* r, const SLev& phat, const SLev& shat, const double* s, const double* t,
+                const double* rhat, const SGeom& S, const Scalars* scal, double* partial, hipStream_t st);
 // FP32 multigrid preconditioner on the spherical grid.  The smoother is
 // zebra phi-line Gauss-Seidel: the lines (i, j) with (i + j) & 1 == colour
 // are solved exactly along phi (a periodic tridiagonal system), with the
@@ -361,8 +367,8 @@ void pbicg_xr(double* x, double* r, const double* phat, const double* shat, cons
 // clearing): 1 = u is taken as zero (first colour), 2 = the pass's own lines
 // are taken as zero (second colour: only its cross-pole term reads them)
 void sph_line_pass(const SLev& L, int colour, int zero_guess, hipStream_t st);
-void sph_residual32(const SLev& L, hipStream_t st);
-void sph_restrict32(const SLev& Lf, const SLev& Lc, hipStream_t st);
+void sph_resrestrict32(const SLev& Lf, const SLev& Lc, hipStream_t st);
+// adds the coarse correction where the colour-1 pass that has to follow reads u
 void sph_prolong_add32(const SLev& Lc, const SLev& Lf, hipStream_t st);
 void sph_coarse32(const double* inv, const SLev& L, hipStream_t st);
 void sph_cast_in(const double* x, const SGeom& S, const SLev& L0, hipStream_t st);
@@ -399,7 +405,8 @@ void n_rhs(const double* rho, long long p0, long long p1, int ghost, double* f, 
            double scale, hipStream_t st);
 void n_to_caller(const double* u, const NGeom& G, double* dst, long long p0, long long p1, int ghost,
                  hipStream_t st);
-int sph_blocks(const SGeom& S);
+int sph_tiles(const SGeom& S);   // blocks of one plane each: the grids the plans accept
+int sph_blocks(const SGeom& S);  // blocks (partial sums) of the kernels that reduce
 void sph_fill_zero(double* x, const SGeom& S, hipStream_t st);
 void sph_copy(const double* src, double* dst, const SGeom& S, hipStream_t st);
 

@@ -304,7 +304,7 @@ int validate(const poisson_grid_t* g, const poisson_opts_t* o) {
     S.nr = g->n[0];
     S.nth = g->n[1];
     S.nph = g->n[2];
-    if (sph_blocks(S) > kPartialCap) {
+    if (sph_tiles(S) > kPartialCap) {
       set_error("grid too large for the reduction buffers");
       return POISSON_EGRID;
     }
@@ -430,6 +430,8 @@ void carve(poisson_plan_s* P, Carver& cv) {
     P->sr = (double*)cv.take(vb);
     P->srh = (double*)cv.take(vb);
     for (int i = 0; i < 2; ++i) {
+      // the multigrid preconditioner keeps phat and shat in FP32
+      if (i == 1 && o.method == POISSON_BICGSTAB_MG32) break;
       P->sp[i] = (double*)cv.take(vb);
       P->sv[i] = (double*)cv.take(vb);
     }
@@ -459,7 +461,7 @@ void carve(poisson_plan_s* P, Carver& cv) {
         const size_t fb = sizeof(float) * (size_t)L.count();
         L.u = (float*)cv.take(fb);
         L.f = (float*)cv.take(fb);
-        L.r = (float*)cv.take(fb);
+        if (lev == 0) L.u2 = (float*)cv.take(fb);
         L.rcl = (const float*)cv.take(sizeof(float) * L.nr);
         L.rcr = (const float*)cv.take(sizeof(float) * L.nr);
         L.cot2 = (const float*)cv.take(sizeof(float) * L.nth);
@@ -921,8 +923,7 @@ const void* vcycle(poisson_plan_s* P, int l, bool zero_guess, hipStream_t st, do
 
 // One FP32 V(nu1, nu2) cycle of the spherical preconditioner from level l on a
 // zero initial guess (colours forward before, backward after the correction).
-void svcycle(poisson_plan_s* P, int l, hipStream_t st) {
-  const SLev& L = P->slv[l];
+void svcycle(poisson_plan_s* P, int l, const SLev& L, hipStream_t st) {
   if (l + 1 == (int)P->slv.size()) {
     sph_coarse32(P->scinv, L, st);
     return;
@@ -933,9 +934,8 @@ void svcycle(poisson_plan_s* P, int l, hipStream_t st) {
   // so u needs no clearing
   for (int s = 0; s < P->opts.nu1; ++s)
     for (int c = 0; c < 2; ++c) sph_line_pass(L, c, s == 0 ? (c == 0 ? 1 : 2) : 0, st);
-  sph_residual32(L, st);
-  sph_restrict32(L, P->slv[l + 1], st);
-  svcycle(P, l + 1, st);
+  sph_resrestrict32(L, P->slv[l + 1], st);
+  svcycle(P, l + 1, P->slv[l + 1], st);
   sph_prolong_add32(P->slv[l + 1], L, st);
   for (int s = 0; s < P->opts.nu2; ++s)
     for (int c = 1; c >= 0; --c) sph_line_pass(L, c, 0, st);
@@ -944,27 +944,32 @@ void svcycle(poisson_plan_s* P, int l, hipStream_t st) {
 // yhat = M^-1 y with M^-1 one FP32 V-cycle (inputs / outputs FP64)
 void sph_precond(poisson_plan_s* P, const double* y, double* yhat, hipStream_t st) {
   sph_cast_in(y, P->S, P->slv[0], st);
-  svcycle(P, 0, st);
+  svcycle(P, 0, P->slv[0], st);
   sph_cast_out(P->slv[0], yhat, P->S, st);
 }
 
-// one right-preconditioned BiCGSTAB iteration with the multigrid preconditioner
+// One right-preconditioned BiCGSTAB iteration with the multigrid
+// preconditioner.  The kernels that form p and s write the cycle's FP32
+// right-hand side as well, and phat and shat stay in the finest level's two
+// solution arrays: as FP64 copies they cost 48 us per cycle at 256 x 128 x 256
+// and twice the bytes where they are read.
 void sph_mg_iteration(poisson_plan_s* P, double* phi, hipStream_t st) {
   const SGeom& S = P->S;
   const int nb = sph_blocks(S);
   double* p = P->sp[0];
-  double* phat = P->sp[1];
   double* v = P->sv[0];
-  double* shat = P->sv[1];
-  pbicg_update_p(P->sr, p, v, S, P->sc, P->scal, st);
-  sph_precond(P, p, phat, st);
-  pbicg_apply(phat, v, P->srh, 0, S, P->sc, P->partial, st);
+  const SLev phat = P->slv[0];
+  SLev shat = phat;
+  shat.u = phat.u2;
+  pbicg_update_p(P->sr, p, v, S, P->sc, P->scal, phat, st);
+  svcycle(P, 0, phat, st);
+  pbicg_apply32(phat, v, P->srh, 0, S, P->sc, P->partial, st);
   bicg_scalars(P->partial, nb, P->scal, 0, st);
-  pbicg_update_s(P->sr, v, P->ss, S, P->sc, P->scal, st);
-  sph_precond(P, P->ss, shat, st);
-  pbicg_apply(shat, P->stt, P->ss, 1, S, P->sc, P->partial, st);
+  pbicg_update_s(P->sr, v, P->ss, S, P->sc, P->scal, shat, st);
+  svcycle(P, 0, shat, st);
+  pbicg_apply32(shat, P->stt, P->ss, 1, S, P->sc, P->partial, st);
   bicg_scalars(P->partial, nb, P->scal, 1, st);
-  pbicg_xr(phi, P->sr, phat, shat, P->ss, P->stt, P->srh, S, P->scal, P->partial, st);
+  pbicg_xr32(phi, P->sr, phat, shat, P->ss, P->stt, P->srh, S, P->scal, P->partial, st);
   bicg_scalars(P->partial, nb, P->scal, 2, st, step_post(P, 0, 8));
 }
 

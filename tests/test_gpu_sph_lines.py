@@ -49,3 +49,30 @@ def test_cycle_matches_oracle_at_every_split(dims, pad):
         err = rel_l2(host(yhat)[:, :, 1:nr + 1], SM.vcycle(y[:, :, 1:nr + 1], lv))
         say(f"  rel L2 {err:.2e} tol {tol:.2e}")
         assert err < tol
+
+
+@pytest.mark.parametrize("method,dims", [("bicgstab", (70, 130, 66)), ("bicgstab", (70, 130, 94)),
+                                         ("bicgstab", (70, 130, 250)), ("bicgstab_mg32", (136, 64, 96)),
+                                         ("bicgstab_mg32", (144, 64, 192))])
+def test_reductions_over_runs_of_planes(method, dims):
+    """Grids whose reducing kernels take 2, 3, 4 and 8 planes per block, the last
+    run shorter: residual and its norm, and the residual BiCGSTAB carries
+    along (its dot products steer it) against that of the solution it returns."""
+    from oracle import operators as OO
+    nr, nth, nph = dims
+    say(f"runs of planes: {method} {dims}")
+    r, th, ph, ds = OM.sph_axes(nr, nth, nph)
+    rng = np.random.default_rng(nph)
+    u, rho = rng.standard_normal((2, nph, nth, nr + 2))
+    plan = pg.Plan(pg.sph_grid(nr, nth, nph), pg.options(method, lmax=-1, max_iter=3))
+    res = torch.zeros(u.shape, dtype=torch.float64, device="cuda:0")
+    n2 = plan.residual(dev(rho), dev(u), res)
+    ref = OO.sph_residual(u, rho, r, ds, th)
+    assert np.max(np.abs(host(res)[:, :, 1:nr + 1] - ref)) < 1e-12 * np.max(np.abs(ref))
+    assert abs(n2 / np.sum(ref ** 2) - 1.0) < 1e-12
+    phi = dev(u)
+    st = plan.solve(dev(rho), phi, tol=1e-30)
+    left = np.linalg.norm(OO.sph_residual(host(phi), rho, r, ds, th))
+    say(f"  {st.iterations} iterations, residual {left:.3e} after {np.linalg.norm(ref):.3e}")
+    # the carried residual drifts by roundings of the start's
+    assert abs(st.rel_residual * st.b_norm - left) < 1e-9 * np.linalg.norm(ref)
