@@ -370,6 +370,27 @@ void sph_line_pass(const SLev& L, int colour, int zero_guess, hipStream_t st);
 void sph_resrestrict32(const SLev& Lf, const SLev& Lc, hipStream_t st);
 // adds the coarse correction where the colour-1 pass that has to follow reads u
 void sph_prolong_add32(const SLev& Lc, const SLev& Lf, hipStream_t st);
+// The levels of a cycle that one workgroup runs in one launch
+// (kernels_sphtail.hip): nl smoothed levels lv[0..nl), lv[nl] solved densely.
+struct SphTail {
+  static constexpr int kLevels = 2;  // the largest first level leaves <= 512 unknowns below the second
+  SLev lv[kLevels + 1];
+  int nl, nu1, nu2;
+  int p1[kLevels + 1];                                   // plane pitch in LDS
+  int u[kLevels + 1], tab[kLevels + 1], f[kLevels + 1];  // byte offsets in LDS
+  bool uniform;                                          // one line table per colatitude
+  size_t lds;
+  const double* inv;
+};
+void sph_tail_split(SLev& L);  // the tail's split of the phi lines
+// arguments of a tail over lv[0..nl), the last one the coarsest; false if it
+// does not fit
+bool sph_tail_args(const SLev* lv, int nl, int nu1, int nu2, SphTail& A);
+bool sph_tail_enable(const SphTail& A);  // call before a launch that may be captured
+// the coarsest inverse as the tail reads it: the rows of k = 0, by column
+void sph_tail_inverse(const SLev& coarsest, const std::vector<double>& inv, std::vector<double>& out);
+// lv[0].u = one V(nu1, nu2) cycle for lv[0].f from a zero guess
+void sph_tail_cycle(const SphTail& A, hipStream_t st);
 void sph_coarse32(const double* inv, const SLev& L, hipStream_t st);
 void sph_cast_in(const double* x, const SGeom& S, const SLev& L0, hipStream_t st);
 void sph_cast_out(const SLev& L0, double* x, const SGeom& S, hipStream_t st);

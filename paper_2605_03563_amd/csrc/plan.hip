@@ -475,17 +475,27 @@ void carve(poisson_plan_s* P, Carver& cv) {
           const int i0 = (int)ceil((p - 0.5 * (h - 1.0)) / h);
           L.ntab = 1 + std::min(std::max(i0, 0), L.nr - 1);
         }
-        if (line_split(L.nph, &L.seg, &L.nseg, &L.nl)) {
-          L.tstride = 4 * L.seg + 4 * L.nseg * L.nseg;
-          const size_t nlines = (size_t)L.nth * L.ntab;
-          L.ltab = (const float*)cv.take(sizeof(float) * (size_t)L.tstride * nlines);
-        }
+        if (line_split(L.nph, &L.seg, &L.nseg, &L.nl)) L.tstride = 4 * L.seg + 4 * L.nseg * L.nseg;
         P->slv.push_back(L);
         ++lev;
       }
       const SLev& C = P->slv.back();
       P->sncoarse = C.nr * C.nth * C.nph;
-      P->scinv = (double*)cv.take(sizeof(double) * (size_t)P->sncoarse * P->sncoarse);
+      // the longest tail of levels that fits one workgroup
+      P->stail = -1;
+      const int nlev = (int)P->slv.size();
+      for (int l = 0; l + 1 < nlev && P->stail < 0; ++l)
+        if (sph_tail_args(P->slv.data() + l, nlev - l, o.nu1, o.nu2, P->stargs)) P->stail = l;
+      for (int l = 0; l < nlev; ++l) {
+        SLev& L = P->slv[l];
+        if (P->stail >= 0 && l >= P->stail && l + 1 < nlev) sph_tail_split(L);
+        if (L.tstride) L.ltab = (const float*)cv.take(sizeof(float) * (size_t)L.tstride * L.nth * L.ntab);
+      }
+      P->scinv = (double*)cv.take(sizeof(double) * (size_t)P->sncoarse * (P->stail < 0 ? P->sncoarse : C.nr * C.nth));
+      if (P->stail >= 0) {
+        sph_tail_args(P->slv.data() + P->stail, nlev - P->stail, o.nu1, o.nu2, P->stargs);
+        P->stargs.inv = P->scinv;
+      }
     }
     return;
   }
@@ -926,6 +936,12 @@ const void* vcycle(poisson_plan_s* P, int l, bool zero_guess, hipStream_t st, do
 void svcycle(poisson_plan_s* P, int l, const SLev& L, hipStream_t st) {
   if (l + 1 == (int)P->slv.size()) {
     sph_coarse32(P->scinv, L, st);
+    return;
+  }
+  if (l == P->stail) {
+    SphTail A = P->stargs;
+    A.lv[0].u = L.u;
+    sph_tail_cycle(A, st);
     return;
   }
   // zero guess: the first colour-0 pass sees u = 0 and writes every colour-0
@@ -1978,6 +1994,14 @@ int poisson_plan(poisson_plan_t* out, const poisson_grid_t* grid, const poisson_
       if (!invert_general(P->sncoarse, A, inv)) {
         set_error("coarsest preconditioner level is singular");
         return fail(POISSON_ENUMERIC);
+      }
+      if (P->stail >= 0 && !sph_tail_enable(P->stargs)) {
+        set_error("the preconditioner's small levels need 160 KB of LDS");
+        return fail(POISSON_EHIP);
+      }
+      if (P->stail >= 0) {
+        sph_tail_inverse(C, inv, A);
+        inv.swap(A);
       }
       if (hipMemcpyAsync(P->scinv, inv.data(), sizeof(double) * inv.size(), hipMemcpyHostToDevice, st) !=
               hipSuccess ||

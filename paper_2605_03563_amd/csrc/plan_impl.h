@@ -71,6 +71,8 @@ struct poisson_plan_s {
   double* srj = nullptr;               // SOR: local Jacobi spectral radius per colatitude
   std::vector<double> srj_host;        // the same on the host
   std::vector<psn::SLev> slv;          // FP32 multigrid preconditioner levels (BICGSTAB_MG32)
+  int stail = -1;                      // its levels stail .. run in one workgroup (-1: none)
+  psn::SphTail stargs{};
   double* scinv = nullptr;             // dense inverse of its coarsest level
   int sncoarse = 0;
   hipGraphExec_t iter_exec = nullptr;  // captured preconditioned BiCGSTAB iteration

@@ -51,6 +51,34 @@ def test_cycle_matches_oracle_at_every_split(dims, pad):
         assert err < tol
 
 
+@pytest.mark.parametrize("pad", [False, True])
+@pytest.mark.parametrize("dims,nu", [((16, 16, 8), (2, 2)), ((16, 12, 12), (2, 2)), ((18, 8, 16), (1, 3)),
+                                     ((16, 8, 20), (2, 1)), ((16, 16, 24), (2, 2)), ((12, 8, 28), (2, 2)),
+                                     ((32, 16, 32), (2, 2)), ((40, 12, 32), (3, 1)), ((64, 24, 32), (2, 2)), ((64, 8, 32), (2, 2))])
+def test_small_levels_in_one_workgroup(dims, nu, pad):
+    """Grids that are, or lead to, levels one workgroup runs: segments of 2 to
+    8 nodes (odd ones restrict across segments), one and two smoothed levels,
+    odd coarsest sizes, all threads busy, sweeps before and after that differ."""
+    nr, nth, nph = dims
+    say(f"small spherical levels: {dims} nu {nu} pad {pad}")
+    args = (nr, 0.2, 1.0)
+    ext = dict(ext_in=nr // 5, ext_out=1, r_pad=0.1)
+    ds = RadialMap(*args, **ext).ds if pad else OM.sph_axes(nr, nth, nph)[3]
+    lv = SM.level0(RadialMap(*args, **ext), nr) if pad else ds
+    grid = pg.sph_grid(nr, nth, nph, 0.2, 1.0, **ext) if pad else pg.sph_grid(nr, nth, nph)
+    plan = pg.Plan(grid, pg.options("bicgstab_mg32", lmax=-1, nu1=nu[0], nu2=nu[1]))
+    tol = max(CYCLE_TOL, 2.0 ** -24 * _line_condition(nr, nth, nph, ds))
+    y = np.zeros((nph, nth, nr + 2))
+    y[:, :, 1:nr + 1] = np.random.default_rng(sum(dims)).standard_normal((nph, nth, nr))
+    yhat = torch.zeros(y.shape, dtype=torch.float64, device="cuda:0")
+    ref = SM.vcycle(y[:, :, 1:nr + 1], lv, nu1=nu[0], nu2=nu[1])
+    for _ in range(2):
+        plan.precond(dev(y), yhat)
+        err = rel_l2(host(yhat)[:, :, 1:nr + 1], ref)
+        say(f"  rel L2 {err:.2e} tol {tol:.2e}")
+        assert err < tol
+
+
 @pytest.mark.parametrize("method,dims", [("bicgstab", (70, 130, 66)), ("bicgstab", (70, 130, 94)),
                                          ("bicgstab", (70, 130, 250)), ("bicgstab_mg32", (136, 64, 96)),
                                          ("bicgstab_mg32", (144, 64, 192))])
