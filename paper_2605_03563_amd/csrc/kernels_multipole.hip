@@ -57,7 +57,10 @@ __device__ inline void regular_solid(double x, double y, double z, double w, dou
   }
 }
 
-// sum_lm q_lm R_lm(x)
+// sum_lm q_lm R_lm(x).  For one m every Q_lm is (x + i y)^m times a real
+// polynomial in z and r^2, so the recurrence over l runs on that alone and the
+// complex factor comes in once per m: 290 FP64 operations at lmax = 8, 500
+// with both parts carried along.
 template <int LMAX>
 __device__ inline double dot_regular(double x, double y, double z, const double* __restrict__ q) {
   const double r2 = x * x + y * y + z * z;
@@ -71,25 +74,20 @@ __device__ inline double dot_regular(double x, double y, double z, const double*
       qr = nr;
       qi = ni;
     }
-    double pr = qr, pi = qi, ppr = 0.0, ppi = 0.0;
+    double p = 1.0, pp = 0.0, sr = 0.0, si = 0.0;
 #pragma unroll
     for (int l = m; l <= LMAX; ++l) {
       if (l > m) {
         const double ca = (2.0 * l - 1.0) / sqrt((double)(l + m) * (double)(l - m));
         const double cb = sqrt((double)(l + m - 1) * (double)(l - m - 1)) / sqrt((double)(l + m) * (double)(l - m));
-        const double cr = ca * z * pr - cb * r2 * ppr;
-        const double ci = ca * z * pi - cb * r2 * ppi;
-        ppr = pr;
-        ppi = pi;
-        pr = cr;
-        pi = ci;
+        const double c = ca * (z * p) - cb * (r2 * pp);
+        pp = p;
+        p = c;
       }
-      if (m == 0) {
-        out += q[l * l + l] * pr;
-      } else {
-        out += 1.4142135623730951 * (q[l * l + l + m] * pr + q[l * l + l - m] * pi);
-      }
+      sr += q[l * l + l + m] * p;
+      if (m > 0) si += q[l * l + l - m] * p;
     }
+    out += m == 0 ? sr : 1.4142135623730951 * (qr * sr + qi * si);
   }
   return out;
 }
@@ -108,7 +106,7 @@ __device__ inline double dot_irregular(double x, double y, double z, const doubl
 //   M_abc = h^3 sum_nodes rho x^a y^b z^c,   a + b + c <= lmax,
 // which factor along the axes: T_b(i,k) = sum_j rho y_j^b (threads along x
 // march y), V_ab(k) = sum_i x_i^a T_b(i,k) (one block per plane), M_abc =
-// sum_k z_k^c V_ab(k) (one block per monomial), and q_lm = sum C_lm^abc M_abc with the
+// sum_k z_k^c V_ab(k), and q_lm = sum C_lm^abc M_abc with the
 // monomial coefficients of R_lm (host table from the same recurrence as
 // regular_solid).  Every sum runs in a fixed order.
 
@@ -158,20 +156,23 @@ __global__ __launch_bounds__(256) void k_mom_rows(const double* __restrict__ rho
   for (int b = 0; b <= LMAX; ++b) out[(long long)b * TP] = acc[b];
 }
 
-// Stage 2: one block per plane k; V[k][ab] for the (a, b) pairs with
+// Stage 2: one block per plane k; V[ab][k] for the (a, b) pairs with
 // a + b <= LMAX in the order a = 0.., b = 0..LMAX-a.  Each wave reduces its
-// products with shuffles, the waves' sums meet in LDS.
+// products with exchanges, the waves' sums meet in LDS.  Bound by latency:
+// with a shuffle sum per pair 18.4 us at 320^3 and 13.8 at 32^3, with shared
+// exchanges 10.1 and 5.1.
 template <int LMAX>
 __global__ __launch_bounds__(256) void k_mom_cols(const double* __restrict__ T, int TP, int n, double h, double x0,
                                                   double* __restrict__ V) {
   constexpr int NAB = (LMAX + 1) * (LMAX + 2) / 2;
+  constexpr int NP = NAB <= 1 ? 1 : NAB <= 4 ? 4 : NAB <= 16 ? 16 : 64;
   __shared__ double red[NAB][4];
   const int E = n - 1;
   const int k = blockIdx.x;
   const int tid = threadIdx.x;
-  double acc[NAB];
+  double acc[NP];
 #pragma unroll
-  for (int q = 0; q < NAB; ++q) acc[q] = 0.0;
+  for (int q = 0; q < NP; ++q) acc[q] = 0.0;
   for (int i = tid; i < E; i += 256) {
     double tb[LMAX + 1];
 #pragma unroll
@@ -191,13 +192,11 @@ __global__ __launch_bounds__(256) void k_mom_cols(const double* __restrict__ T, 
       xa *= x;
     }
   }
-#pragma unroll
-  for (int q = 0; q < NAB; ++q) {
-    const double w = wave_sum(acc[q]);
-    if ((tid & 63) == 0) red[q][tid >> 6] = w;
-  }
+  const double w = wave_sums<NP>(acc);
+  const int q = (tid & 63) / (64 / NP);
+  if (q < NAB) red[q][tid >> 6] = w;
   __syncthreads();
-  if (tid < NAB) V[(long long)k * NAB + tid] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
+  if (tid < NAB) V[(long long)tid * E + k] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
 }
 
 // Stage 3: one block per monomial u = (a, b, c) (packed a | b << 4 | c << 8
@@ -205,7 +204,6 @@ __global__ __launch_bounds__(256) void k_mom_cols(const double* __restrict__ T, 
 template <int LMAX>
 __global__ __launch_bounds__(256) void k_mom_z(const double* __restrict__ V, int n, double h, double z0,
                                                const int* __restrict__ mono, double* __restrict__ M) {
-  constexpr int NAB = (LMAX + 1) * (LMAX + 2) / 2;
   const int E = n - 1;
   const int u = blockIdx.x;
   const int a = mono[u] & 15, b = (mono[u] >> 4) & 15, c = (mono[u] >> 8) & 15;
@@ -215,7 +213,7 @@ __global__ __launch_bounds__(256) void k_mom_z(const double* __restrict__ V, int
     const double z = z0 + k * h;
     double zc = 1.0;
     for (int e = 0; e < c; ++e) zc *= z;
-    s += zc * V[(long long)k * NAB + ab];
+    s += zc * V[(long long)ab * E + k];
   }
   s = block_sum(s);
   if (threadIdx.x == 0) M[u] = s * (h * h * h);
@@ -363,38 +361,37 @@ __global__ __launch_bounds__(256) void k_sph_theta(const double* __restrict__ G,
 }
 
 // Every ghost node of the Cartesian node array: z ghost planes, then y ghost
-// rows of the interior planes, then x ghost ends of the interior rows.
+// rows of the interior planes, then x ghost ends of the interior rows.  Bound
+// by the expansion's FP64 operations (320^3 with three layers, 1.9 million
+// nodes: 29.8 us; 36.2 with both parts of every Q_lm and 64-bit index
+// divisions; two nodes per thread, which share the moments, 36.4).
 template <int LMAX>
 __global__ __launch_bounds__(256) void k_cart_ghosts(double* __restrict__ phi, long long p0, long long p1, int n,
                                                      int g, double h, double lo, double cx, double cy, double cz,
                                                      const double* __restrict__ q, double G) {
   const int E = n - 1;
   const int M = E + 2 * g;
-  const long long nA = 2LL * g * M * M;
-  const long long nB = (long long)E * 2 * g * M;
-  const long long nC = (long long)E * E * 2 * g;
-  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  const unsigned nA = 2u * g * M * M, nB = (unsigned)E * 2 * g * M, nC = (unsigned)E * E * 2 * g;
+  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= nA + nB + nC) return;
   int a, b, k;
   if (t < nA) {
-    const int p = (int)(t / ((long long)M * M));
-    const int rem = (int)(t % ((long long)M * M));
+    const unsigned row = t / M;
+    const int p = row / M;
     k = p < g ? p : g + E + (p - g);
-    b = rem / M;
-    a = rem % M;
+    b = row - p * M;
+    a = t - row * M;
   } else if (t < nA + nB) {
-    const long long u = t - nA;
-    k = g + (int)(u / (2LL * g * M));
-    const int rem = (int)(u % (2LL * g * M));
-    const int qq = rem / M;
+    const unsigned u = t - nA, row = u / M, p = row / (2 * g);
+    k = g + p;
+    const int qq = row - p * 2 * g;
     b = qq < g ? qq : g + E + (qq - g);
-    a = rem % M;
+    a = u - row * M;
   } else {
-    const long long u = t - nA - nB;
-    k = g + (int)(u / ((long long)E * 2 * g));
-    const int rem = (int)(u % ((long long)E * 2 * g));
-    b = g + rem / (2 * g);
-    const int qq = rem % (2 * g);
+    const unsigned u = t - nA - nB, row = u / (2 * g), p = row / E;
+    k = g + p;
+    b = g + row - p * E;
+    const int qq = u - row * 2 * g;
     a = qq < g ? qq : g + E + (qq - g);
   }
   const int sh = g - 1;

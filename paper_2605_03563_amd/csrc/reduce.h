@@ -37,6 +37,28 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
+// Sums over the wavefront of N values per lane (a power of two up to 64): lane
+// L gets that of value L / (64 / N).  Lanes 32, 16, .. apart swap the halves
+// they do not keep, so 64 sums take 63 exchanges instead of 384.
+template <int N, int D = 32>
+__device__ inline double wave_sums(double (&a)[N]) {
+  if constexpr (D == 0) {
+    return a[0];
+  } else if constexpr (N == 1) {
+    a[0] += __shfl_xor(a[0], D, 64);
+    return wave_sums<1, D / 2>(a);
+  } else {
+    const bool hi = (threadIdx.x & D) != 0;
+    double b[N / 2];
+#pragma unroll
+    for (int q = 0; q < N / 2; ++q) {
+      const double keep = hi ? a[q + N / 2] : a[q], give = hi ? a[q] : a[q + N / 2];
+      b[q] = keep + __shfl_xor(give, D, 64);
+    }
+    return wave_sums<N / 2, D / 2>(b);
+  }
+}
+
 // Sum over the block (blockDim multiple of 64, <= 1024) in a fixed order;
 // result valid in thread 0.
 __device__ inline double block_sum(double v) {
