@@ -190,6 +190,12 @@ int resrestrict19(const void* phi, const void* f, bool f32, const Geom& Gf, void
 void residual(const void* phi, const void* f, bool in_f32, void* r_out, bool out_f32, const Geom& G,
               int order, bool zero_unknowns_in, double* partial, hipStream_t st, int colour = -1);
 int residual_blocks(const Geom& G);   // partials written by residual()
+// r = scale rho - L u on the caller's arrays (natural order, pitches p0 and p1,
+// G's ghost layers; r must not overlap u), star_blocks partial sums of r^2;
+// without rho: r = L u, no sums
+int star_blocks(const Geom& G);
+void star_residual(const double* u, const double* rho, double* r, long long p0, long long p1, const Geom& G,
+                   double scale, double* partial, hipStream_t st);
 // f_coarse = R (f - L phi) for the 7-point operator without storing the fine
 // residual; resrestrict_ok tells whether the level's shape is supported
 // (two colours, one ghost layer, at most 256 intervals)

@@ -2161,6 +2161,15 @@ static int need_cart(poisson_plan_t P) {
   return POISSON_OK;
 }
 
+// Whether an operator can run on the caller's arrays as they are: in and out
+// apart (the copies of the split layout allow a result in place of an input)
+// and few enough blocks for the partial sums.
+static bool star_direct(const poisson_plan_s* P, const double* in, const double* out) {
+  const size_t bytes = sizeof(double) * (size_t)P->grid.pitch[1] * P->G0.M;
+  const char *a = (const char*)in, *b = (const char*)out;
+  return (a + bytes <= b || b + bytes <= a) && star_blocks(P->G0) <= kPartialCap;
+}
+
 int poisson_op_apply(poisson_plan_t P, const double* d_phi, double* d_out) {
   if (!P || !d_phi || !d_out) {
     set_error("null argument");
@@ -2176,6 +2185,10 @@ int poisson_op_apply(poisson_plan_t P, const double* d_phi, double* d_out) {
     return POISSON_EINVAL;
   }
   const poisson_grid_t& g = P->grid;
+  if (star_direct(P, d_phi, d_out)) {
+    star_residual(d_phi, nullptr, d_out, g.pitch[0], g.pitch[1], P->G0, 1.0, nullptr, st);
+    return launch_check("poisson_op_apply");
+  }
   split_from_natural(d_phi, g.pitch[0], g.pitch[1], P->phi64, false, P->G0, 1.0, st);
   fill_zero(P->f64, false, P->G0.total(), st);
   residual(P->phi64, P->f64, false, P->t64, false, P->G0, P->order, false, nullptr, st);
@@ -2201,6 +2214,10 @@ int poisson_op_residual(poisson_plan_t P, const double* d_rho, const double* d_p
     n27_residual((const double*)L.u, (const double*)L.f, (double*)L.r, L.G, L.A, P->partial, st);
     finish_sum(P->partial, (int)n27_blocks(L.G), 1, P->scal, kRes2, st);
     n_to_caller((const double*)L.r, L.G, d_res, g.pitch[0], g.pitch[1], g.ghost, st);
+  } else if (star_direct(P, d_phi, d_res) && star_direct(P, d_rho, d_res)) {
+    const poisson_grid_t& g = P->grid;
+    star_residual(d_phi, d_rho, d_res, g.pitch[0], g.pitch[1], P->G0, P->opts.four_pi_G, P->partial, st);
+    finish_sum(P->partial, star_blocks(P->G0), 1, P->scal, kRes2, st);
   } else {
     const poisson_grid_t& g = P->grid;
     split_from_natural(d_phi, g.pitch[0], g.pitch[1], P->phi64, false, P->G0, 1.0, st);
