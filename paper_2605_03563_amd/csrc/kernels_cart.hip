@@ -62,6 +62,15 @@ inline dim3 staged_grid(const Geom& G) {
   return dim3((mc + BX - 1) / BX, (E + TBY - 1) / TBY, (E + kz - 1) / kz);
 }
 
+// (compact column, row) of a 256-thread block's lane on flat_grid; false past
+// the last pair
+__device__ inline bool flat_pair(const Geom& G, int bx, int tid, int& m, int& b) {
+  const unsigned mc = G.mhi() - G.mlo() + 1, t = bx * 256 + tid, row = t / mc;
+  m = G.mlo() + (int)(t - row * mc);
+  b = G.g + (int)row;
+  return (int)row < G.n - 1;
+}
+
 __device__ inline int planes_per_block(const Geom& G) { return (G.n - 1 + (int)gridDim.z - 1) / (int)gridDim.z; }
 
 
@@ -1793,20 +1802,21 @@ __global__ __launch_bounds__(256) void k_cg_dir19(const double* __restrict__ R, 
 // (b, k) for KZP planes, forms p = sr r + beta p_old at every position it
 // loads (both colours at compact m for the z-window, x- and y-neighbours per
 // plane; ghosts of r and p_old are zero), issues a chunk's loads before its
-// updates, then stores p_new and q = -L p and sums p . q.
+// updates, then stores p_new and q = -L p and sums p . q.  Lanes are numbered
+// over (compact column, row) pairs, as in k_cg_upd: 150^3 33.6 us with padded
+// rows, 28.8 here.
 template <int KZP>
 __global__ __launch_bounds__(256) void k_cg_dir7(const double* __restrict__ Rr, const double* __restrict__ Pold,
                                                  double* __restrict__ Pnew, double* __restrict__ Q, Geom G,
                                                  double ih2, double sr, const Scalars* __restrict__ scal,
                                                  double* __restrict__ partial) {
-  int bx, by, bz;
+  int bx, by, bz, m, b;
   xcd_block(bx, by, bz);
-  const int m = G.mlo() + bx * BX + (int)threadIdx.x;
-  const int b = G.g + by * BY + (int)threadIdx.y;
+  const bool live = flat_pair(G, bx, threadIdx.x, m, b);
   const int last = G.g + G.n - 2;
   const double beta = scal->v[2];
   double acc = 0.0;
-  if (m <= G.mhi() && b <= last) {
+  if (live) {
     const int kz = planes_per_block(G);
     const int k0 = G.g + bz * kz;
     const int k1 = min(k0 + kz - 1, last);
@@ -1867,7 +1877,7 @@ __global__ __launch_bounds__(256) void k_cg_dir7(const double* __restrict__ Rr, 
     }
   }
   const double sum = block_sum(acc);
-  if (threadIdx.x == 0 && threadIdx.y == 0) partial[linear_block()] = sum;
+  if (threadIdx.x == 0) partial[linear_block()] = sum;
 }
 
 // CG direction and operator, 7-point, with two compact columns m0, m0+1 per
@@ -2025,23 +2035,27 @@ __global__ __launch_bounds__(BX* BY) void k_cg_dir7z(const double* __restrict__ 
 // x -= alpha p; r -= alpha q; partial (r . r).  The vectors follow the
 // residual r = f - L x (the negative of the residual of the SPD system
 // -L x = -f), so the direction enters x with a minus sign.
+// Lanes are numbered over (compact column, row) pairs: at 150^3 a row of 75
+// columns left 41% of the lanes of padded rows idle (28.2 us; 27.5 here).
+template <int C>
 __global__ __launch_bounds__(256) void k_cg_upd(double* __restrict__ X, double* __restrict__ R,
                                                 const double* __restrict__ P, const double* __restrict__ Q,
                                                 Geom G, const Scalars* __restrict__ scal,
                                                 double* __restrict__ partial) {
-  int bx, by, bz;
+  int bx, by, bz, m, b;
   xcd_block(bx, by, bz);
-  const int m = G.mlo() + bx * BX + (int)threadIdx.x;
-  const int b = G.g + by * BY + (int)threadIdx.y;
+  const bool live = flat_pair(G, bx, threadIdx.x, m, b);
   const int last = G.g + G.n - 2;
   const double alpha = scal->v[3];
   double acc = 0.0;
-  if (m <= G.mhi() && b <= last) {
+  if (live) {
     const int kz = planes_per_block(G);
     const int k1 = min(G.g + bz * kz + kz - 1, last);
+#pragma unroll 2
     for (int k = G.g + bz * kz; k <= k1; ++k)
-      for (int r = 0; r < G.C; ++r) {
-        const int a = (m << G.lc) + r;
+#pragma unroll
+      for (int r = 0; r < C; ++r) {
+        const int a = C * m + r;
         if (!G.inner(a)) continue;
         const long long i = G.at(a, b, k);
         X[i] -= alpha * P[i];
@@ -2051,7 +2065,7 @@ __global__ __launch_bounds__(256) void k_cg_upd(double* __restrict__ X, double* 
       }
   }
   const double s = block_sum(acc);
-  if (threadIdx.x == 0 && threadIdx.y == 0) partial[linear_block()] = s;
+  if (threadIdx.x == 0) partial[linear_block()] = s;
 }
 
 // partial sums of -(r . z): with the CG residual rho = -r and the
@@ -2507,7 +2521,7 @@ static dim3 cg_dir_vec_grid(const Geom& G) {
 }
 
 int cg_dir_blocks(const Geom& G, int order) {
-  return (int)nblocks(cg_dir_vec(G, order) ? cg_dir_vec_grid(G) : col_grid(G));
+  return (int)nblocks(cg_dir_vec(G, order) ? cg_dir_vec_grid(G) : order == 2 ? flat_grid(G) : col_grid(G));
 }
 
 void cg_direction_apply(const double* r, const double* p_old, double* p_new, double* q, const Geom& G, int order,
@@ -2520,9 +2534,9 @@ void cg_direction_apply(const double* r, const double* p_old, double* p_new, dou
       k_cg_dir7z<8><<<cg_dir_vec_grid(G), dim3(BX, BY), 0, st>>>(r, p_old, p_new, q, G, ih2, sr, scal, partial);
   }
   else if (order == 2 && kz_for(G) == KZ)
-    k_cg_dir7<KZ><<<col_grid(G), dim3(BX, BY), 0, st>>>(r, p_old, p_new, q, G, ih2, sr, scal, partial);
+    k_cg_dir7<KZ><<<flat_grid(G), 256, 0, st>>>(r, p_old, p_new, q, G, ih2, sr, scal, partial);
   else if (order == 2)
-    k_cg_dir7<1><<<col_grid(G), dim3(BX, BY), 0, st>>>(r, p_old, p_new, q, G, ih2, sr, scal, partial);
+    k_cg_dir7<1><<<flat_grid(G), 256, 0, st>>>(r, p_old, p_new, q, G, ih2, sr, scal, partial);
   else
     k_cg_dir19<<<col_grid(G), dim3(BX, BY), 0, st>>>(r, p_old, p_new, q, G, ih2, sr, scal, partial);
 }
@@ -2533,8 +2547,12 @@ void pcg_dot(const double* r, const double* z, const Geom& G, double* partial, h
 
 void cg_update(double* x, double* r, const double* p, const double* q, const Geom& G, const Scalars* scal,
                double* partial, hipStream_t st) {
-  k_cg_upd<<<col_grid(G), dim3(BX, BY), 0, st>>>(x, r, p, q, G, scal, partial);
+  if (G.C == 2)
+    k_cg_upd<2><<<flat_grid(G), 256, 0, st>>>(x, r, p, q, G, scal, partial);
+  else
+    k_cg_upd<4><<<flat_grid(G), 256, 0, st>>>(x, r, p, q, G, scal, partial);
 }
+int cg_update_blocks(const Geom& G) { return (int)nblocks(flat_grid(G)); }
 
 void cg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipStream_t st, Post post) {
   k_cg_scalars<<<1, kFinishThreads, 0, st>>>(partial, nb, scal, stage, post);

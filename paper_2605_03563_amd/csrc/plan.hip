@@ -1505,7 +1505,6 @@ int solve_cart(poisson_plan_s* P, const double* rho, double* phi, double tol, po
     // L z = r (r = -rho) from z = 0; the direction is built from -z so the
     // CG kernels keep their signs (x -= alpha p, r -= alpha q); the inner
     // product rho . zeta = -(r . z) sits in v[kRR], ||r||^2 in v[kRes2].
-    const int cb = cg_blocks(G);
     finish_sum(P->partial, pcg_precondition(P, st), 1, P->scal, kRR, st);
     const double zero = 0.0;
     HIPCHK(hipMemcpyAsync(&P->scal->v[2], &zero, sizeof(double), hipMemcpyHostToDevice, st));
@@ -1516,12 +1515,11 @@ int solve_cart(poisson_plan_s* P, const double* rho, double* phi, double tol, po
       cg_direction_apply(P->cz, pold, pnew, P->cq, G, P->order, P->scal, P->partial, st, -1.0);
       cg_scalars(P->partial, cg_dir_blocks(G, P->order), P->scal, 0, st);
       cg_update(P->phi64, P->cr, pnew, P->cq, G, P->scal, P->partial, st);
-      finish_sum(P->partial, cb, 1, P->scal, kRes2, st, checked(check, kRes2));
+      finish_sum(P->partial, cg_update_blocks(G), 1, P->scal, kRes2, st, checked(check, kRes2));
       cg_scalars(P->partial, pcg_precondition(P, st), P->scal, 1, st);
       std::swap(pold, pnew);
     }));
   } else if (o.method == POISSON_CG) {
-    const int cb = cg_blocks(G);
     // rr = r.r ; beta = 0 ; p_old = 0
     finish_sum(P->partial, nb, 1, P->scal, kRR, st);
     const double zero = 0.0;
@@ -1533,7 +1531,7 @@ int solve_cart(poisson_plan_s* P, const double* rho, double* phi, double tol, po
       cg_direction_apply(P->cr, pold, pnew, P->cq, G, P->order, P->scal, P->partial, st);
       cg_scalars(P->partial, cg_dir_blocks(G, P->order), P->scal, 0, st);
       cg_update(P->phi64, P->cr, pnew, P->cq, G, P->scal, P->partial, st);
-      cg_scalars(P->partial, cb, P->scal, 1, st, checked(check, kRR));
+      cg_scalars(P->partial, cg_update_blocks(G), P->scal, 1, st, checked(check, kRR));
       std::swap(pold, pnew);
     }));
   } else {  // multigrid
