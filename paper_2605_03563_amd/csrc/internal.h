@@ -204,6 +204,9 @@ bool resrestrict_ok(const Geom& Gf);
 // came last) and only the colour-0 ones are formed.
 void resrestrict(const void* phi, const void* f, bool f32, const Geom& Gf, void* f_coarse, const Geom& Gc,
                  hipStream_t st, bool r0only = false);
+// the same with r0only, one coarse row per wavefront (kernels_rr7.hip)
+void resrestrict7_rows(const void* phi, const void* f, bool f32, const Geom& Gf, void* f_coarse, const Geom& Gc,
+                       hipStream_t st);
 // last_zero (four colours): the residuals of colour 3 vanish (a Gauss-Seidel
 // pass over it came last) and are not read
 void restrict_fw(const void* r_fine, const Geom& Gf, void* f_coarse, const Geom& Gc, bool f32,

@@ -1434,10 +1434,13 @@ static void resrestrict7_go(const T* phi, const T* f, const Geom& Gf, T* fc, con
   const int nc = Gc.n;
   const T ih2 = (T)(1.0 / (Gf.h * Gf.h));
   const dim3 grid(1, (nc - 1 + TYC - 1) / TYC, (nc - 1 + KZC - 1) / KZC), blk(BXR, 2 * TYC + 1);
-  if (r0)
-    k_resrestrict7<T, BXR, TYC, KZC, true><<<grid, blk, 0, st>>>(phi, f, Gf, fc, Gc, ih2);
-  else
-    k_resrestrict7<T, BXR, TYC, KZC, false><<<grid, blk, 0, st>>>(phi, f, Gf, fc, Gc, ih2);
+  if constexpr (BXR == 64 && KZC == 1) {
+    if (r0) {
+      k_resrestrict7<T, BXR, TYC, KZC, true><<<grid, blk, 0, st>>>(phi, f, Gf, fc, Gc, ih2);
+      return;
+    }
+  }
+  k_resrestrict7<T, BXR, TYC, KZC, false><<<grid, blk, 0, st>>>(phi, f, Gf, fc, Gc, ih2);
 }
 
 // Large levels: several coarse rows and planes per block (little recomputed
@@ -2347,7 +2350,11 @@ bool resrestrict_ok(const Geom& Gf) { return Gf.C == 2 && Gf.g == 1 && Gf.n >= 4
 
 void resrestrict(const void* phi, const void* f, bool f32, const Geom& Gf, void* f_coarse, const Geom& Gc,
                  hipStream_t st, bool r0only) {
-  if (f32)
+  // by rows from 33 compact columns (below, its wavefronts are half empty, and
+  // the legs of small levels rarely leave such a level to this call)
+  if (r0only && Gf.mhi() + 1 > 32)
+    resrestrict7_rows(phi, f, f32, Gf, f_coarse, Gc, st);
+  else if (f32)
     resrestrict7_t<float>((const float*)phi, (const float*)f, Gf, (float*)f_coarse, Gc, r0only, st);
   else
     resrestrict7_t<double>((const double*)phi, (const double*)f, Gf, (double*)f_coarse, Gc, r0only, st);
