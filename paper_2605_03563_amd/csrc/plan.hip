@@ -430,8 +430,8 @@ void carve(poisson_plan_s* P, Carver& cv) {
     P->sr = (double*)cv.take(vb);
     P->srh = (double*)cv.take(vb);
     for (int i = 0; i < 2; ++i) {
-      // the multigrid preconditioner keeps phat and shat in FP32
-      if (i == 1 && o.method == POISSON_BICGSTAB_MG32) break;
+      // (i = 1: phat and shat; with the multigrid preconditioner, which keeps
+      // them in FP32, they only hold the workspace at the size callers know)
       P->sp[i] = (double*)cv.take(vb);
       P->sv[i] = (double*)cv.take(vb);
     }
