@@ -2323,6 +2323,9 @@ int poisson_op_restrict_residual(poisson_plan_t P, const double* d_rho, const do
   }
   finish_sum(P->partial, nb, 1, P->scal, kRes2, st);
   split_to_dense(L1.f, f32, d_coarse, L1.G, st);
+  // x held Phi with its ghost values; the corrections of later cycles, which
+  // live there, have a zero boundary
+  if (f32) fill_zero(L0.phi, true, P->G0.total(), st);
   CHK(launch_check("poisson_op_restrict_residual"));
   if (h_norm2) {
     CHK(read_scalars(P, kRes2, 1));
