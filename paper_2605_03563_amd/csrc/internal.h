@@ -123,7 +123,7 @@ struct W4 {
 
 // Per-plan device scalars used by the Krylov solvers and reductions.
 struct Scalars {
-  double v[32];
+  double v[31];
   unsigned seq;  // number of the last post
   int stop;      // the residual has met the solve's tolerance
 };
@@ -230,6 +230,7 @@ struct TailArgs {
   int nl, nu1, nu2;
   int clear;     // elements of the potentials, zeroed at the start
   int N, parts;  // coarsest unknowns, threads per row of its inverse
+  int rows;      // doubles of the table of the threads' rows
   int blocks;    // entries of the inverse's blocks
   int staged;    // byte offset of their copy in LDS (0: too many for it)
   int f, r;      // LDS offsets (elements) of the right-hand sides below the top and of the residual

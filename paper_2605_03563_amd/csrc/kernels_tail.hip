@@ -169,16 +169,22 @@ __device__ inline T full_weight(const T* r, int I, int J, int K) {
   return acc + q * ry(1);
 }
 
-// What thread p N + q does in the coarsest solve (a table of one entry per
-// thread precedes the blocks): it multiplies the columns p, p + parts, ... of
-// row q of the blocks (sector by sector).
+// What thread p N + q does in the coarsest solve (a table of the N parts
+// threads that do anything precedes the blocks): it multiplies the columns p,
+// p + parts, ... of row q of the blocks (sector by sector).
 struct CoarseRow {
   int row;   // natural index of row q | first row of its sector << 16
   int part;  // size of the sector | p << 16 (size 0: nothing to do)
   int col;   // entry (j, q) of the block at col + j size
   int ijk;   // coordinates of the node with natural index q, eight bits each
 };
-constexpr size_t kRowTable = kTailThreads * sizeof(CoarseRow) / sizeof(double);
+// Threads per row: no more than the largest sector has columns, so that few
+// unknowns (1, 8 or 27) don't leave one thread a thousand empty parts to add up.
+inline int coarse_parts(int E) { return std::min(kTailThreads / (E * E * E), sector_size(E, 0)); }
+// doubles of the table; a single unknown's row needs none
+inline size_t row_table(int E) {
+  return E == 1 ? 0 : (size_t)E * E * E * coarse_parts(E) * sizeof(CoarseRow) / sizeof(double);
+}
 
 // Coarsest solve: f (pitch ED) into e, natural order with pitch ED + 2 and a
 // layer of zeros around the unknowns.  v: N + 1024 doubles; blocks: in LDS, or
@@ -332,8 +338,9 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const T* __restrict__ F, 
       fr[c][i] = a < V::g + E ? F[c * cs + row + (a >> V::lc)] : (T)0;
     }
   }
-  const CoarseRow R = reinterpret_cast<const CoarseRow*>(pinv)[tid];
-  const double* blocks = pinv + kRowTable;
+  CoarseRow R = {0, tid < A.N ? 1 : 0, 0, 0};  // a single unknown
+  if (A.rows) R = tid < A.N * A.parts ? reinterpret_cast<const CoarseRow*>(pinv)[tid] : CoarseRow{0, 0, 0, 0};
+  const double* blocks = pinv + A.rows;
   if (A.staged) {
     double* staged = reinterpret_cast<double*>(smem + A.staged);
     for (int i = tid; i < A.blocks; i += kTailThreads) staged[i] = blocks[i];
@@ -453,7 +460,8 @@ bool tail_args(const Geom* lev, int nl, bool f32, int nu1, int nu2, TailArgs& A)
   A.nu1 = nu1;
   A.nu2 = nu2;
   A.N = Ec * Ec * Ec;
-  A.parts = kTailThreads / A.N;
+  A.parts = coarse_parts(Ec);
+  A.rows = (int)row_table(Ec);
   A.blocks = (int)block_entries(Ec);
   for (int l = 0; l < nl; ++l) {
     A.d[l].n = lev[l].n;
@@ -469,7 +477,7 @@ bool tail_enable(bool f32, int C, int n) {
   return f32 ? tail_lds<float, 4>(n) : tail_lds<double, 4>(n);
 }
 
-size_t tail_blocks_size(int E) { return kRowTable + block_entries(E); }
+size_t tail_blocks_size(int E) { return row_table(E) + block_entries(E); }
 
 void tail_blocks(int E, const std::vector<double>& inv, std::vector<double>& out) {
   const int N = E * E * E, H = E / 2;
@@ -527,15 +535,14 @@ void tail_blocks(int E, const std::vector<double>& inv, std::vector<double>& out
       rows.push_back(CoarseRow{id[q] | base << 16, size, first[sector_odd(s)] + q, 0});
   }
   for (int q = 0; q < N; ++q) rows[q].ijk = q % E | (q / E % E) << 8 | (q / (E * E)) << 16;
-  for (int t = N; t < kTailThreads; ++t) {
+  for (int t = N; t < N * coarse_parts(E); ++t) {
     CoarseRow r = rows[t % N];
-    const int p = t / N;
-    r.part = p < kTailThreads / N ? r.part | p << 16 : 0;
+    r.part |= t / N << 16;
     rows.push_back(r);
   }
   out.assign(tail_blocks_size(E), 0.0);
-  memcpy(out.data(), rows.data(), rows.size() * sizeof(CoarseRow));
-  std::copy(entries.begin(), entries.end(), out.begin() + kRowTable);
+  memcpy(out.data(), rows.data(), row_table(E) * sizeof(double));
+  std::copy(entries.begin(), entries.end(), out.begin() + row_table(E));
 }
 
 void tail_cycle(const void* f, void* x, bool f32, const Geom& G, const TailArgs& A, const double* pinv,
