@@ -1643,41 +1643,56 @@ __global__ __launch_bounds__(256) void k_coarse(const double* __restrict__ inv, 
 }
 
 // ---------------------------------------------------------------- conversions
-// Natural order to the colour-split layout and back, bound by HBM.  A thread
-// takes one (a, b) of kConv consecutive planes, their loads underway together;
-// (a, b) pairs are numbered over the whole plane, so that a ragged row leaves
-// no lanes idle.  201^3 star layout, FP64: 37 and 39 us with one node per
-// thread and rows padded to 64 lanes, 32.5 and 29.6 here.
+// Natural order to the colour-split layout and back, bound by HBM on large
+// grids and by the launch on small ones.  A thread takes one (a, b) of Q
+// consecutive planes, their loads underway together; with Q = kConv the (a, b)
+// pairs are numbered over the whole plane, so that a ragged row leaves no lanes
+// idle.  201^3 star layout, FP64: 37 and 39 us with Q = 1 and rows padded to 64
+// lanes, 32.5 and 29.6 with Q = kConv.
 constexpr int kConv = 4;
-template <typename T>
+// the first node of the thread; false: none
+template <int Q>
+__device__ inline bool conv_node(const Geom& G, int& a, int& b, int& k0) {
+  if constexpr (Q == 1) {
+    a = blockIdx.x * BX + threadIdx.x;
+    b = blockIdx.y * BY + threadIdx.y;
+    k0 = blockIdx.z;
+    return a < G.M && b < G.M;
+  } else {
+    int bx, by, bz;
+    xcd_block(bx, by, bz);
+    const int t = bx * 256 + (int)threadIdx.x;
+    b = t / G.M;
+    a = t - b * G.M;
+    k0 = bz * Q;
+    return b < G.M;
+  }
+}
+
+template <typename T, int Q>
 __global__ __launch_bounds__(256) void k_split(const double* __restrict__ src, long long p0, long long p1,
                                                T* __restrict__ dst, Geom G, double scale) {
-  int bx, by, bz;
-  xcd_block(bx, by, bz);
-  const int t = bx * 256 + (int)threadIdx.x, b = t / G.M, a = t - b * G.M;
-  if (b >= G.M) return;
-  const int k0 = bz * kConv;
-  double v[kConv];
+  int a, b, k0;
+  if (!conv_node<Q>(G, a, b, k0)) return;
+  double v[Q];
 #pragma unroll
-  for (int q = 0; q < kConv; ++q) v[q] = src[(long long)min(k0 + q, G.M - 1) * p1 + (long long)b * p0 + a];
+  for (int q = 0; q < Q; ++q) v[q] = src[(long long)min(k0 + q, G.M - 1) * p1 + (long long)b * p0 + a];
 #pragma unroll
-  for (int q = 0; q < kConv; ++q)
+  for (int q = 0; q < Q; ++q)
     if (k0 + q < G.M) dst[G.at(a, b, k0 + q)] = (T)(scale * v[q]);
 }
 
+template <int Q>
 __global__ __launch_bounds__(256) void k_merge(const double* __restrict__ src, double* __restrict__ dst,
                                                long long p0, long long p1, Geom G, int unknowns_only,
                                                double scale) {
-  int bx, by, bz;
-  xcd_block(bx, by, bz);
-  const int t = bx * 256 + (int)threadIdx.x, b = t / G.M, a = t - b * G.M;
-  if (b >= G.M || (unknowns_only && !(G.inner(a) && G.inner(b)))) return;
-  const int k0 = bz * kConv;
-  double v[kConv];
+  int a, b, k0;
+  if (!conv_node<Q>(G, a, b, k0) || (unknowns_only && !(G.inner(a) && G.inner(b)))) return;
+  double v[Q];
 #pragma unroll
-  for (int q = 0; q < kConv; ++q) v[q] = src[G.at(a, b, min(k0 + q, G.M - 1))];
+  for (int q = 0; q < Q; ++q) v[q] = src[G.at(a, b, min(k0 + q, G.M - 1))];
 #pragma unroll
-  for (int q = 0; q < kConv; ++q) {
+  for (int q = 0; q < Q; ++q) {
     const int k = k0 + q;
     if (k < G.M && (!unknowns_only || G.inner(k))) dst[(long long)k * p1 + (long long)b * p0 + a] = scale * v[q];
   }
@@ -1747,6 +1762,8 @@ __global__ __launch_bounds__(256) void k_dense_split(const double* __restrict__ 
 }
 
 // ---------------------------------------------------------------- reductions
+// POST: the scalars are posted (2.9 us on small grids; 2.6 without the code for it)
+template <bool POST>
 __global__ __launch_bounds__(kFinishThreads) void k_finish(const double* __restrict__ partial, int nb, int nslots,
                                                            Scalars* __restrict__ scal, int dst, Post post) {
   for (int slot = 0; slot < nslots; ++slot) {
@@ -1754,7 +1771,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish(const double* __restr
     if (threadIdx.x == 0) scal->v[dst + slot] = s;
     __syncthreads();
   }
-  if (threadIdx.x == 0) post_scalars(scal, post);
+  if (POST && threadIdx.x == 0) post_scalars(scal, post);
 }
 
 // ---------------------------------------------------------------- CG (A = -L)
@@ -2143,18 +2160,35 @@ Geom make_geom(int n, int g, int C, double h) {
 }
 
 static dim3 conv_grid(const Geom& G) { return dim3((G.M * G.M + 255) / 256, 1, (G.M + kConv - 1) / kConv); }
+// one node per thread up to 81 nodes per axis: split, split and merge take 11.9
+// us at 81 (12.8 with four planes per thread), 14.3 at 85 (13.7), 11.5 at 9
+// (13.2, the divisions of the XCD order and of the pairs)
+static bool conv_small(const Geom& G) { return G.M <= 81; }
+static dim3 conv_small_grid(const Geom& G) { return dim3((G.M + BX - 1) / BX, (G.M + BY - 1) / BY, G.M); }
+
+template <typename T>
+static void split_t(const double* src, long long p0, long long p1, T* dst, const Geom& G, double scale,
+                    hipStream_t st) {
+  if (conv_small(G))
+    k_split<T, 1><<<conv_small_grid(G), dim3(BX, BY), 0, st>>>(src, p0, p1, dst, G, scale);
+  else
+    k_split<T, kConv><<<conv_grid(G), 256, 0, st>>>(src, p0, p1, dst, G, scale);
+}
 
 void split_from_natural(const double* src, long long p0, long long p1, void* dst, bool dst_f32,
                         const Geom& G, double scale, hipStream_t st) {
   if (dst_f32)
-    k_split<float><<<conv_grid(G), 256, 0, st>>>(src, p0, p1, (float*)dst, G, scale);
+    split_t(src, p0, p1, (float*)dst, G, scale, st);
   else
-    k_split<double><<<conv_grid(G), 256, 0, st>>>(src, p0, p1, (double*)dst, G, scale);
+    split_t(src, p0, p1, (double*)dst, G, scale, st);
 }
 
 void merge_to_natural(const double* src, double* dst, long long p0, long long p1, const Geom& G,
                       bool unknowns_only, double scale, hipStream_t st) {
-  k_merge<<<conv_grid(G), 256, 0, st>>>(src, dst, p0, p1, G, unknowns_only ? 1 : 0, scale);
+  if (conv_small(G))
+    k_merge<1><<<conv_small_grid(G), dim3(BX, BY), 0, st>>>(src, dst, p0, p1, G, unknowns_only ? 1 : 0, scale);
+  else
+    k_merge<kConv><<<conv_grid(G), 256, 0, st>>>(src, dst, p0, p1, G, unknowns_only ? 1 : 0, scale);
 }
 
 void fill_zero(void* x, bool f32, long long count, hipStream_t st) {
@@ -2510,7 +2544,10 @@ void split_to_dense(const void* split, bool f32, double* dense, const Geom& G, h
 
 void finish_sum(const double* partial, int nb, int nslots, Scalars* scal, int dst, hipStream_t st,
                 Post post) {
-  k_finish<<<1, kFinishThreads, 0, st>>>(partial, nb, nslots, scal, dst, post);
+  if (post.mail)
+    k_finish<true><<<1, kFinishThreads, 0, st>>>(partial, nb, nslots, scal, dst, post);
+  else
+    k_finish<false><<<1, kFinishThreads, 0, st>>>(partial, nb, nslots, scal, dst, post);
 }
 
 int cg_blocks(const Geom& G) { return (int)nblocks(col_grid(G)); }
