@@ -7,6 +7,9 @@
 // cl = a - b/2, cr = a + b/2 come per radial index from tables; radial ghosts hold Dirichlet values,
 // the colatitude neighbour past a pole is the node at phi + pi, phi is
 // periodic.  Direction vectors keep zero radial ghosts.
+#include <algorithm>
+#include <type_traits>
+
 #include "internal.h"
 #include "reduce.h"
 
@@ -49,6 +52,20 @@ inline dim3 rgrid(const SGeom& S) {
   return g;
 }
 
+// The thread's column and planes.  Without RUNS (a plane per block) the grid is
+// taken as it is: on small grids the divisions of the XCD order and of the run
+// are 0.8 us of a residual's 8 (64 x 32 x 80).
+template <bool RUNS>
+__device__ inline void column(const SGeom& S, int& i, int& j, int& k0, int& k1) {
+  int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+  if constexpr (RUNS) xcd_block(bx, by, bz);
+  i = 1 + bx * BX + threadIdx.x;
+  j = by * BY + threadIdx.y;
+  const int kz = RUNS ? (S.nph + gridDim.z - 1) / gridDim.z : 1;
+  k0 = bz * kz;
+  k1 = RUNS ? min(k0 + kz, S.nph) : k0 + 1;
+}
+
 // Calls out(k, A u) for the planes k0 .. k1-1 of column (i, j): along phi a
 // plane's value is the next one's neighbour.
 template <class F, class O>
@@ -79,18 +96,15 @@ __device__ inline bool active(const SGeom& S, int i, int j, int k) {
   return i >= 1 && i <= S.nr && j < S.nth && k < S.nph;
 }
 
-template <bool ZU>
+template <bool RUNS, bool ZU>
 __global__ __launch_bounds__(256) void k_sph_residual(const double* __restrict__ U, const double* __restrict__ rho,
                                                       double* __restrict__ R, SGeom S, Coef c,
                                                       const double* __restrict__ cot2,
                                                       const double* __restrict__ isin2,
                                                       const double* __restrict__ r2, double fpg,
                                                       double* __restrict__ partial) {
-  int bx, by, bz;
-  xcd_block(bx, by, bz);
-  const int i = 1 + bx * BX + threadIdx.x;
-  const int j = by * BY + threadIdx.y;
-  const int kz = (S.nph + gridDim.z - 1) / gridDim.z, k0 = bz * kz, k1 = min(k0 + kz, S.nph);
+  int i, j, k0, k1;
+  column<RUNS>(S, i, j, k0, k1);
   double acc = 0.0;
   if (i <= S.nr && j < S.nth) {
     auto V = [&](int ii, int jj, int kk) -> double {
@@ -245,15 +259,12 @@ struct HatF {
 // mode 1: partial0 += out.a, partial1 += out.out (a = s).  HBM-bound (20 bytes
 // per unknown with an FP32 xhat): 256 x 128 x 256
 // 57 us (70-73 with an FP64 xhat, a block per plane and no XCD order).
-template <int MODE, class H>
+template <bool RUNS, int MODE, class H>
 __global__ __launch_bounds__(256) void k_apply_dot(H Xh, double* __restrict__ Out, const double* __restrict__ Aw,
                                                    SGeom S, Coef c, const double* __restrict__ cot2,
                                                    const double* __restrict__ isin2, double* __restrict__ partial) {
-  int bx, by, bz;
-  xcd_block(bx, by, bz);
-  const int i = 1 + bx * BX + threadIdx.x;
-  const int j = by * BY + threadIdx.y;
-  const int kz = (S.nph + gridDim.z - 1) / gridDim.z, k0 = bz * kz, k1 = min(k0 + kz, S.nph);
+  int i, j, k0, k1;
+  column<RUNS>(S, i, j, k0, k1);
   double a0 = 0.0, a1 = 0.0;
   if (i <= S.nr && j < S.nth)
     sph_op_column(Xh, S, c, cot2, isin2, i, j, k0, k1, [&](int k, double o) {
@@ -273,16 +284,13 @@ __global__ __launch_bounds__(256) void k_apply_dot(H Xh, double* __restrict__ Ou
 // x += alpha phat + omega shat;  r = s - omega t;  partial0 += rhat.r, partial1 += r.r
 // (HBM-bound: 56 bytes per unknown with FP32 phat, shat; 256 x 128 x 256 88 us,
 // 107 with FP64 copies)
-template <class H>
+template <bool RUNS, class H>
 __global__ __launch_bounds__(256) void k_pbicg_xr(double* __restrict__ X, double* __restrict__ R, H Ph, H Sh,
                                                   const double* __restrict__ Sv, const double* __restrict__ T,
                                                   const double* __restrict__ Rhat, SGeom S,
                                                   const Scalars* __restrict__ scal, double* __restrict__ partial) {
-  int bx, by, bz;
-  xcd_block(bx, by, bz);
-  const int i = 1 + bx * BX + threadIdx.x;
-  const int j = by * BY + threadIdx.y;
-  const int kz = (S.nph + gridDim.z - 1) / gridDim.z, k0 = bz * kz, k1 = min(k0 + kz, S.nph);
+  int i, j, k0, k1;
+  column<RUNS>(S, i, j, k0, k1);
   const double alpha = scal->v[1], omega = scal->v[2];
   double a0 = 0.0, a1 = 0.0;
   if (i <= S.nr && j < S.nth)
@@ -677,15 +685,26 @@ int sph_blocks(const SGeom& S) {
   return (int)(g.x * g.y * g.z);
 }
 
+// go(whether blocks take runs of planes)
+template <class Go>
+static void by_runs(const SGeom& S, const Go& go) {
+  if ((int)rgrid(S).z < S.nph)
+    go(std::true_type());
+  else
+    go(std::false_type());
+}
+
 void sph_residual(const double* u, const double* rho, double* r, const SGeom& S, const SphCoef& c,
                   double four_pi_G, bool zu, double* partial, hipStream_t st) {
   const Coef cf = make_coef(S, c);
-  if (zu)
-    k_sph_residual<true><<<rgrid(S), dim3(BX, BY), 0, st>>>(u, rho, r, S, cf, c.cot, c.isin2, c.r2, four_pi_G,
-                                                           partial);
-  else
-    k_sph_residual<false><<<rgrid(S), dim3(BX, BY), 0, st>>>(u, rho, r, S, cf, c.cot, c.isin2, c.r2, four_pi_G,
-                                                            partial);
+  by_runs(S, [&](auto runs) {
+    if (zu)
+      k_sph_residual<runs, true><<<rgrid(S), dim3(BX, BY), 0, st>>>(u, rho, r, S, cf, c.cot, c.isin2, c.r2,
+                                                                    four_pi_G, partial);
+    else
+      k_sph_residual<runs, false><<<rgrid(S), dim3(BX, BY), 0, st>>>(u, rho, r, S, cf, c.cot, c.isin2, c.r2,
+                                                                     four_pi_G, partial);
+  });
 }
 
 void sph_apply(const double* u, double* out, const SGeom& S, const SphCoef& c, hipStream_t st) {
@@ -720,10 +739,12 @@ template <class H>
 static void apply_dot(const H& xhat, double* out, const double* w, int mode, const SGeom& S, const SphCoef& c,
                       double* partial, hipStream_t st) {
   const Coef cf = make_coef(S, c);
-  if (mode == 0)
-    k_apply_dot<0><<<rgrid(S), dim3(BX, BY), 0, st>>>(xhat, out, w, S, cf, c.cot, c.isin2, partial);
-  else
-    k_apply_dot<1><<<rgrid(S), dim3(BX, BY), 0, st>>>(xhat, out, w, S, cf, c.cot, c.isin2, partial);
+  by_runs(S, [&](auto runs) {
+    if (mode == 0)
+      k_apply_dot<runs, 0><<<rgrid(S), dim3(BX, BY), 0, st>>>(xhat, out, w, S, cf, c.cot, c.isin2, partial);
+    else
+      k_apply_dot<runs, 1><<<rgrid(S), dim3(BX, BY), 0, st>>>(xhat, out, w, S, cf, c.cot, c.isin2, partial);
+  });
 }
 
 void pbicg_apply(const double* xhat, double* out, const double* w, int mode, const SGeom& S, const SphCoef& c,
@@ -737,11 +758,16 @@ void pbicg_apply32(const SLev& xhat, double* out, const double* w, int mode, con
 
 void pbicg_xr(double* x, double* r, const double* phat, const double* shat, const double* s, const double* t,
               const double* rhat, const SGeom& S, const Scalars* scal, double* partial, hipStream_t st) {
-  k_pbicg_xr<<<rgrid(S), dim3(BX, BY), 0, st>>>(x, r, HatD{phat, S}, HatD{shat, S}, s, t, rhat, S, scal, partial);
+  by_runs(S, [&](auto runs) {
+    k_pbicg_xr<runs><<<rgrid(S), dim3(BX, BY), 0, st>>>(x, r, HatD{phat, S}, HatD{shat, S}, s, t, rhat, S, scal,
+                                                        partial);
+  });
 }
 void pbicg_xr32(double* x, double* r, const SLev& phat, const SLev& shat, const double* s, const double* t,
                 const double* rhat, const SGeom& S, const Scalars* scal, double* partial, hipStream_t st) {
-  k_pbicg_xr<<<rgrid(S), dim3(BX, BY), 0, st>>>(x, r, HatF{phat}, HatF{shat}, s, t, rhat, S, scal, partial);
+  by_runs(S, [&](auto runs) {
+    k_pbicg_xr<runs><<<rgrid(S), dim3(BX, BY), 0, st>>>(x, r, HatF{phat}, HatF{shat}, s, t, rhat, S, scal, partial);
+  });
 }
 
 void bicg_scalars(const double* partial, int nb, Scalars* scal, int stage, hipStream_t st, Post post) {
