@@ -834,7 +834,10 @@ void w4_matrix(const W4& w, int n, std::vector<double>& A) {
 
 // ------------------------------------------------------------ solver pieces
 // A post of scalars first .. first + count - 1 by a step of a solve (not counted
-// here: a recorded step is enqueued later and more than once).
+// here: a recorded step is enqueued later and more than once).  Whoever
+// enqueues it counts it in P->posted before: a launch may queue its work and
+// still report an error, and the next solve's first post needs a number that
+// no post has had.
 Post step_post(const poisson_plan_s* P, int first = kRes2, int count = 1) {
   Post p;
   p.mail = P->mail;
@@ -1382,8 +1385,8 @@ int solve_spai(poisson_plan_s* P, const double* rho, double* phi, double tol, po
   int it = 0;
   bool conv = rel <= tol;
   while (!conv && it < o.max_iter) {
-    CHK(launch_step(P));
     ++P->posted;
+    CHK(launch_step(P));
     ++it;
     if (it % o.check_every == 0 || it == o.max_iter) {
       CHK(wait_post(P, P->posted, 1));
@@ -1446,9 +1449,9 @@ int solve_cart(poisson_plan_s* P, const double* rho, double* phi, double tol, po
         do {
           ++sent;
           check = sent % o.check_every == 0 || sent == o.max_iter;
+          if (check) ++P->posted;
           step(check);
         } while (!check);
-        ++P->posted;
         due[waiting] = P->posted;
         last[waiting++] = sent;
         CHK(launch_check(what));
@@ -1537,8 +1540,8 @@ int solve_cart(poisson_plan_s* P, const double* rho, double* phi, double tol, po
   } else {  // multigrid
     const bool split = split_cycle(P);
     while (!conv && it < o.max_iter) {
-      CHK(split ? launch_split(P, it == 0) : launch_step(P));
       ++P->posted;
+      CHK(split ? launch_split(P, it == 0) : launch_step(P));
       ++it;
       if (it % o.check_every == 0 || it == o.max_iter) {
         CHK(wait_post(P, P->posted, 1));
@@ -1618,9 +1621,9 @@ int solve_sph_sor(poisson_plan_s* P, const double* rho, double* phi, double tol,
     sph_sor_sweep(P, rho, phi, st);
     ++it;
     if (it % o.check_every == 0 || it == o.max_iter) {
+      ++P->posted;
       sph_residual(phi, rho, nullptr, S, P->sc, o.four_pi_G, false, P->partial, st);
       finish_sum(P->partial, nb, 1, P->scal, kRes2, st, step_post(P));
-      ++P->posted;
       CHK(launch_check("spherical SOR"));
       CHK(wait_post(P, P->posted, 1));
       rel = rel_of(P->host[0], T.bnorm);
@@ -1692,6 +1695,7 @@ int solve_sph(poisson_plan_s* P, const double* rho, double* phi, double tol, poi
   const bool mg_graph = mg && capture_stream(P) != nullptr;
   if (mg_graph) CHK(capture_sph_iteration(P, phi));
   while (!conv && it < o.max_iter) {
+    ++P->posted;
     if (mg_graph) {
       HIPCHK(hipGraphLaunch(P->iter_exec, st));
     } else if (mg) {
@@ -1706,7 +1710,6 @@ int solve_sph(poisson_plan_s* P, const double* rho, double* phi, double tol, poi
       pbicg_xr(phi, P->sr, phat, shat, P->ss, P->stt, P->srh, S, P->scal, P->partial, st);
       bicg_scalars(P->partial, nb, P->scal, 2, st, step_post(P, 0, 8));
     }
-    ++P->posted;
     ++it;
     if (!(it % o.check_every == 0 || it == o.max_iter)) continue;
     {
@@ -1756,7 +1759,10 @@ int psn::cart_step(poisson_plan_s* P, bool use_graph) {
     set_error("multigrid plan expected");
     return POISSON_EINVAL;
   }
-  if (use_graph) return launch_step(P);
+  if (use_graph) {
+    ++P->posted;
+    return launch_step(P);
+  }
   first_pass(P, P->st);
   mg_step(P, P->st, Post());
   return launch_check("multigrid step");
