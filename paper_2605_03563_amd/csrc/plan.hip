@@ -1464,7 +1464,6 @@ int solve_cart(poisson_plan_s* P, const double* rho, double* phi, double tol, po
       rel = rel_of(P->host[0], T.bnorm);
       T.push(rel);
       if (!isfinite(rel)) {
-        HIPCHK(hipStreamSynchronize(st));
         set_error("%s %s (non-finite residual)", what, failure);
         return POISSON_ENUMERIC;
       }
@@ -2131,7 +2130,12 @@ int poisson_solve(poisson_plan_t P, const double* d_rho, double* d_phi, const po
   int s = P->sph                               ? solve_sph(P, d_rho, d_phi, tol, stats)
           : !P->nlv.empty()                   ? solve_spai(P, d_rho, d_phi, tol, stats)
                                                : solve_cart(P, d_rho, d_phi, tol, stats);
-  if (stats && s < 0) stats->status = s;
+  if (s < 0) {
+    // the host reads posts while kernels run: what is still queued on the
+    // caller's arrays, the workspace and the mailbox ends here
+    (void)hipStreamSynchronize(P->st);
+    if (stats) stats->status = s;
+  }
   return s;
 }
 

@@ -94,3 +94,31 @@ def test_post_left_by_a_failed_launch(runtime):
         status, st = solve()
         assert status == L.WARN_MAXITER and st.b_norm == 3.0, (name, status, st.b_norm)
     """)
+
+
+def test_nothing_runs_after_an_error(runtime):
+    """A solve that gives up has waited for what it queued: the caller may free
+    its arrays, the workspace and the plan."""
+    _run(runtime, """
+    for name, solve, _ in cases():
+        b2.value, r2.value = 4.0, float("nan")
+        assert solve()[0] == L.ENUMERIC, name
+        assert rt.host_running() == 0, name
+        r2.value, fail.value = 1.0, 1
+        status, st = solve()
+        assert status == (L.WARN_MAXITER if fail.value else L.EHIP), name
+        assert rt.host_running() == 0, name
+        fail.value = 0
+    """)
+
+
+def test_diverging_solve_has_ended(runtime):
+    """The same where the residual stops being finite on the way."""
+    _run(runtime, """
+    for name, solve, _ in cases():
+        b2.value, r2.value = 4.0, 1.0
+        turns.value, later.value = 3, float("nan")
+        assert solve()[0] == L.ENUMERIC, name
+        assert rt.host_running() == 0, name
+        turns.value = 0
+    """)
