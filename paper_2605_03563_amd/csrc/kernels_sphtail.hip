@@ -133,7 +133,11 @@ __device__ inline void pass_on(const SLev& L, int p1, const Share& s, const Spot
   const int lane = threadIdx.x & 63;
   E[lane] = y[0];
   E[64 + lane] = y[SL - 1];
+  // the ends are read by other lanes of the wavefront: the barrier alone orders
+  // no memory
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   entries(tb + 4 * SL + (2 * (kSeg - 1) + 1) * 2 * kSeg, gl);  // rows of segment 0's neighbours
   entries(tb + 4 * SL + 2 * 2 * kSeg, gr);
   float xl = 0.0f, xr = 0.0f;
