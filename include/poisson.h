@@ -305,9 +305,14 @@ int poisson_op_prolong_add(poisson_plan_t plan, const double* d_coarse, double* 
 int poisson_op_vcycle(poisson_plan_t plan, const double* d_rho, double* d_phi, int32_t cycles);
 
 /* `sweeps` forward Gauss-Seidel sweeps (omega = 1) on the plan's resident
-   fine-level arrays exactly as the last poisson_solve / poisson_op_* call
-   left them, with no layout conversion: the smoother kernel alone, for
-   timing it in its solver launch configuration.  MG / MG_IR32 plans sweep
+   fine-level arrays, with no layout conversion: the smoother kernel alone,
+   for timing it in its solver launch configuration.  The arrays are as the
+   last poisson_solve, poisson_op_smooth, poisson_op_vcycle or
+   poisson_op_restrict_residual call left them (zero before any; the last
+   leaves an MG_IR32 plan's correction at zero), on MG_SPAI plans also
+   poisson_op_residual.  On other plans poisson_op_residual and
+   poisson_op_apply work on the caller's arrays; only where a result overlaps
+   an input do they load the FP64 ones.  MG / MG_IR32 plans sweep
    their cycle's finest level (FP64 or FP32); MG_SPAI plans take 2 * sweeps
    fused SPAI steps (out of place, so the result returns to where it
    started) on theirs; other Cartesian plans sweep the FP64 potential. */
