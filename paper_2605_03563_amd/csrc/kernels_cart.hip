@@ -198,7 +198,8 @@ template <> struct VecOf<float, 2> { typedef float type __attribute__((ext_vecto
 // colour shift r the node of column m is a = 2m + r: its x-neighbours are the
 // other colour at columns m and m - 1 (r = 0) or m + 1 (r = 1), from the
 // lane's own vector except at its ends, where the neighbouring lanes supply
-// them (the wavefront's edge lanes load theirs).  ZG: the other colour is
+// them (the wavefront's edge lanes and the row's last one, whose neighbour
+// holds no part of the row, load theirs).  ZG: the other colour is
 // taken as zero.  DOT: also the block's partial sum of -(f . x_new) over the
 // updated nodes, as k_pass7.
 template <typename T, int CPL, bool ZG, int KZP, bool DOT>
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(256) void k_pass7v(T* __restrict__ X, const T* __re
   V ym[KZP], yp[KZP], fv[KZP];
   T xe[KZP];
   const bool needl = lane == 0 && mm >= 1;
-  const bool needr = lane == BX - 1 && mm + CPL < G.W;
+  const bool needr = (lane == BX - 1 || mm + CPL > G.mhi()) && mm + CPL < G.W;
 #pragma unroll
   for (int t = 0; t < KZP; ++t) {
     const int k = min(k0 + t, k1);
@@ -259,7 +260,7 @@ __global__ __launch_bounds__(256) void k_pass7v(T* __restrict__ X, const T* __re
       T lft = __shfl_up(z[t + 1][CPL - 1], 1, 64);
       T rgt = __shfl_down(z[t + 1][0], 1, 64);
       if (lane == 0) lft = xe[t];
-      if (lane == BX - 1) rgt = xe[t];
+      if (needr) rgt = xe[t];
 #pragma unroll
       for (int i = 0; i < CPL; ++i) {
         const T xs = r == 0 ? (i == 0 ? lft : z[t + 1][i - 1]) : (i == CPL - 1 ? rgt : z[t + 1][i + 1]);
