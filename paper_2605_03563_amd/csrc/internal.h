@@ -216,7 +216,9 @@ void restrict_fw(const void* r_fine, const Geom& Gf, void* f_coarse, const Geom&
 // own colour and overwrites them all.
 void prolong_add(const void* e_coarse, const Geom& Gc, void* phi_fine, const Geom& Gf, bool f32,
                  hipStream_t st, bool c0only = false);
-void coarse_solve(const double* inv, const void* f, void* phi, bool f32, const Geom& G, hipStream_t st);
+// (add: phi += inv f instead of phi = inv f, here and in the two below)
+void coarse_solve(const double* inv, const void* f, void* phi, bool f32, const Geom& G, hipStream_t st,
+                  bool add = false);
 // phi64 (unknowns) += e (f32 or f64)
 void add_correction(double* phi, const void* e, bool e_f32, const Geom& G, hipStream_t st);
 
@@ -426,10 +428,10 @@ void n_resrestrict(const void* u, const void* f, bool f32, const NGeom& G, const
 void n_copy(const void* a, void* b, bool f32, const NGeom& G, hipStream_t st);
 void n_prolong_add(const void* uc, bool f32_coarse, const NGeom& Gc, void* uf, bool f32_fine, const NGeom& Gf,
                    hipStream_t st);
-void n_coarse(const double* inv, const void* f, void* u, bool f32, const NGeom& G, hipStream_t st);
+void n_coarse(const double* inv, const void* f, void* u, bool f32, const NGeom& G, hipStream_t st, bool add);
 // coarsest level by CG to relative residual rtol (one block, LDS resident)
 size_t n_cg_lds_bytes(const NGeom& G);
-void n_coarse_cg(const void* f, void* u, bool f32, const NGeom& G, const W4& A, double rtol, hipStream_t st);
+void n_coarse_cg(const void* f, void* u, bool f32, const NGeom& G, const W4& A, double rtol, hipStream_t st, bool add);
 // caller arrays (pitches p0, p1; `ghost` layers) <-> level arrays
 void n_from_caller(const double* src, long long p0, long long p1, int ghost, double* u, const NGeom& G,
                    bool zero_inner, hipStream_t st);

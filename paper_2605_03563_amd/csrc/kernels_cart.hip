@@ -1623,9 +1623,10 @@ __global__ __launch_bounds__(256) void k_prolong2(const T* __restrict__ Ec, Geom
 
 // e = A_c^{-1} f on the coarsest level: one wavefront per row of the dense
 // FP64 inverse; FP32 levels are cast in and out (the solve itself is FP64).
+// add: x += e.
 template <typename T>
 __global__ __launch_bounds__(256) void k_coarse(const double* __restrict__ inv, const T* __restrict__ F,
-                                                T* __restrict__ X, Geom G) {
+                                                T* __restrict__ X, Geom G, int add) {
   const int E = G.n - 1;
   const int N = E * E * E;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -1639,7 +1640,8 @@ __global__ __launch_bounds__(256) void k_coarse(const double* __restrict__ inv, 
   acc = wave_sum(acc);
   if (lane == 0) {
     const int ii = row % E, jj = (row / E) % E, kk = row / (E * E);
-    X[G.at(ii + G.g, jj + G.g, kk + G.g)] = (T)acc;
+    T* x = X + G.at(ii + G.g, jj + G.g, kk + G.g);
+    *x = (T)(add ? (double)*x + acc : acc);
   }
 }
 
@@ -2508,14 +2510,14 @@ void prolong_add(const void* e_coarse, const Geom& Gc, void* phi_fine, const Geo
   }
 }
 
-void coarse_solve(const double* inv, const void* f, void* phi, bool f32, const Geom& G, hipStream_t st) {
+void coarse_solve(const double* inv, const void* f, void* phi, bool f32, const Geom& G, hipStream_t st, bool add) {
   const int E = G.n - 1;
   const int N = E * E * E;
   const dim3 grid((N + 3) / 4);
   if (f32)
-    k_coarse<float><<<grid, 256, 0, st>>>(inv, (const float*)f, (float*)phi, G);
+    k_coarse<float><<<grid, 256, 0, st>>>(inv, (const float*)f, (float*)phi, G, add);
   else
-    k_coarse<double><<<grid, 256, 0, st>>>(inv, (const double*)f, (double*)phi, G);
+    k_coarse<double><<<grid, 256, 0, st>>>(inv, (const double*)f, (double*)phi, G, add);
 }
 
 void add_correction(double* phi, const void* e, bool e_f32, const Geom& G, hipStream_t st) {

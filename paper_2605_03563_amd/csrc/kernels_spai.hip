@@ -329,10 +329,11 @@ __global__ __launch_bounds__(BX* BY) void k_nprolong(const TC* __restrict__ uc, 
   }
 }
 
-// coarsest level: u = A^-1 f with the dense inverse, one wavefront per row
+// coarsest level: u = A^-1 f with the dense inverse, one wavefront per row;
+// add (here and below): u += A^-1 f
 template <typename T>
 __global__ __launch_bounds__(256) void k_ncoarse(const double* __restrict__ inv, const T* __restrict__ f,
-                                                 T* __restrict__ u, NGeom G) {
+                                                 T* __restrict__ u, NGeom G, int add) {
   const int E = G.n - 1;
   const int N = E * E * E;
   const int row = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
@@ -346,7 +347,8 @@ __global__ __launch_bounds__(256) void k_ncoarse(const double* __restrict__ inv,
   acc = wave_sum(acc);
   if (lane == 0) {
     const int i = row % E, j = (row / E) % E, k = row / (E * E);
-    u[G.at(i + 1, j + 1, k + 1)] = (T)acc;
+    T* x = u + G.at(i + 1, j + 1, k + 1);
+    *x = (T)(add ? (double)*x + acc : acc);
   }
 }
 
@@ -357,7 +359,7 @@ __global__ __launch_bounds__(256) void k_ncoarse(const double* __restrict__ inv,
 // order.
 template <typename T>
 __global__ __launch_bounds__(1024) void k_ncg(const T* __restrict__ f, T* __restrict__ u, NGeom G, W4 A,
-                                              double rtol, int maxit) {
+                                              double rtol, int maxit, int add) {
   extern __shared__ double sh[];
   __shared__ double bc;
   const int E = G.n - 1, EP = E + 2, N = E * E * E;
@@ -426,7 +428,7 @@ __global__ __launch_bounds__(1024) void k_ncg(const T* __restrict__ f, T* __rest
     __syncthreads();
     rr = rr_new;
   }
-  for (int c = tid; c < N; c += nt) u[at(c)] = (T)x[c];
+  for (int c = tid; c < N; c += nt) u[at(c)] = (T)(add ? (double)u[at(c)] + x[c] : x[c]);
 }
 
 // caller node array (one ghost layer, pitches p0, p1) -> level array;
@@ -607,13 +609,13 @@ void n_prolong_add(const void* uc, bool f32_coarse, const NGeom& Gc, void* uf, b
     k_nprolong<double, float><<<gr, bl, 0, st>>>((const double*)uc, Gc, (float*)uf, Gf);
 }
 
-void n_coarse(const double* inv, const void* f, void* u, bool f32, const NGeom& G, hipStream_t st) {
+void n_coarse(const double* inv, const void* f, void* u, bool f32, const NGeom& G, hipStream_t st, bool add) {
   const int E = G.n - 1;
   const int N = E * E * E;
   if (f32)
-    k_ncoarse<float><<<(N + 3) / 4, 256, 0, st>>>(inv, (const float*)f, (float*)u, G);
+    k_ncoarse<float><<<(N + 3) / 4, 256, 0, st>>>(inv, (const float*)f, (float*)u, G, add);
   else
-    k_ncoarse<double><<<(N + 3) / 4, 256, 0, st>>>(inv, (const double*)f, (double*)u, G);
+    k_ncoarse<double><<<(N + 3) / 4, 256, 0, st>>>(inv, (const double*)f, (double*)u, G, add);
 }
 
 size_t n_cg_lds_bytes(const NGeom& G) {
@@ -621,14 +623,15 @@ size_t n_cg_lds_bytes(const NGeom& G) {
   return sizeof(double) * (EP * EP * EP + 3 * E * E * E);
 }
 
-void n_coarse_cg(const void* f, void* u, bool f32, const NGeom& G, const W4& A, double rtol, hipStream_t st) {
+void n_coarse_cg(const void* f, void* u, bool f32, const NGeom& G, const W4& A, double rtol, hipStream_t st,
+                 bool add) {
   const int E = G.n - 1;
   const int maxit = 2 * E * E * E;
   const size_t lds = n_cg_lds_bytes(G);
   if (f32)
-    k_ncg<float><<<1, 1024, lds, st>>>((const float*)f, (float*)u, G, A, rtol, maxit);
+    k_ncg<float><<<1, 1024, lds, st>>>((const float*)f, (float*)u, G, A, rtol, maxit, add);
   else
-    k_ncg<double><<<1, 1024, lds, st>>>((const double*)f, (double*)u, G, A, rtol, maxit);
+    k_ncg<double><<<1, 1024, lds, st>>>((const double*)f, (double*)u, G, A, rtol, maxit, add);
 }
 
 // Caller arrays hold `ghost` layers; node 0 of the level (the first ghost

@@ -894,7 +894,14 @@ const void* vcycle(poisson_plan_s* P, int l, bool zero_guess, hipStream_t st, do
     return L.phi;
   }
   if (l + 1 == (int)P->lv.size()) {
-    coarse_solve(P->cinv, L.f, L.phi, f32, L.G, st);
+    if (zero_guess) {
+      coarse_solve(P->cinv, L.f, L.phi, f32, L.G, st);
+    } else {
+      // the only level: the inverse is that of the operator with zero ghost
+      // values, and the potential's enter through the residual
+      residual(L.phi, L.f, f32, L.tmp, f32, L.G, P->order, false, nullptr, st);
+      coarse_solve(P->cinv, L.tmp, L.phi, f32, L.G, st, true);
+    }
     return L.phi;
   }
   if (legs_ok(L.G, o.nu1, o.nu2)) {
@@ -1042,10 +1049,15 @@ void* spai_smooth(NLevel& L, void* cur, int steps, hipStream_t st, bool zero = f
 void spai_vcycle(poisson_plan_s* P, int l, hipStream_t st) {
   NLevel& L = P->nlv[l];
   if (l + 1 == (int)P->nlv.size()) {
+    // the only level solves for a correction of u, whose ghost values enter
+    // through the residual
+    const bool only = l == 0;
+    if (only) n27_residual((const double*)L.u, (const double*)L.f, (double*)L.r, L.G, L.A, P->partial, st);
+    const void* f = only ? L.r : L.f;
     if (P->opts.coarse_tol > 0.0)
-      n_coarse_cg(L.f, L.u, L.f32, L.G, L.A, P->opts.coarse_tol, st);
+      n_coarse_cg(f, L.u, L.f32, L.G, L.A, P->opts.coarse_tol, st, only);
     else
-      n_coarse(P->cinv, L.f, L.u, L.f32, L.G, st);
+      n_coarse(P->cinv, f, L.u, L.f32, L.G, st, only);
     return;
   }
   if (l > 0 && P->opts.nu1 == 0) fill_zero(L.u, L.f32, L.G.total(), st);
