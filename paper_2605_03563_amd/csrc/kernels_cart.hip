@@ -2349,7 +2349,9 @@ static void residual_t(const T* phi, const T* f, TO* r, const Geom& G, int order
     // count equals the staged grid's
     bool two_col = false;
     if constexpr (sizeof(TO) == 4) two_col = !zu && G.n >= 256 && mb == 1;
-    if (zu)
+    if (sg.x == 0) {
+      // two intervals: the one unknown lies in column 0
+    } else if (zu)
       k_residual<T, TO, 6, true><<<sg, sb, 0, st>>>(phi, f, r, G, ih2, partial, mb);
     else if (two_col) {
       if constexpr (sizeof(TO) == 4)
