@@ -60,7 +60,8 @@ __host__ __device__ inline int groups(const Geom& G) { return ((G.M - 1) >> 2) /
 // holds the centre plane of the block's positions with up(e) rows before and
 // dn(e) rows after them, so every x- and y-neighbour is one read at a fixed
 // distance.  A plane's result is stored one plane later, after the wait for
-// the loads: stores are never waited for.
+// the loads: the store has a plane's time before the next wait, which counts
+// stores with the loads.
 template <typename T, int BP, bool ZM>
 __global__ __launch_bounds__(BP, 4) void k_pass19w(T* __restrict__ X, const T* __restrict__ F, Geom G,
                                                                    int c, T h2, int zmask) {
@@ -215,7 +216,8 @@ __global__ __launch_bounds__(BP, 4) void k_pass19w(T* __restrict__ X, const T* _
 }
 
 
-// Lanes per block: the twelve halo rows take one chunk per lane, the reason why
+// Lanes per block: the twelve halo rows take one chunk per lane (256 lanes up to
+// 163 intervals in FP64 and 331 in FP32, 512 up to 331 and 667), the reason why
 // wide levels want large blocks -- a second chunk per lane spills, and a spill
 // waits for every load underway (FP64 at 511^3 with 512 lanes: 321-380 us
 // against 297 with 1024).  0: too wide for any.

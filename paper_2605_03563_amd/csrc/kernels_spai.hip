@@ -511,7 +511,9 @@ void n27_residual(const double* u, const double* f, double* r, const NGeom& G, c
 // enough wavefronts.  Step at 127^3 20 us with (R, kz) = (4, 4), 23 with (2, 4), 29
 // with (4, 16); at 255^3 108 with (4, 16), 125 with (4, 4), 125 with (2, 16);
 // at 511^3 804 with (4, 32), 888 with (2, 32), 956 with (4, 256); at 31^3 5.8
-// with (2, 1), 7.8 with (2, 4); at 63^3 8.2 with (2, 4), 11 with (2, 1).
+// with (2, 1), 7.8 with (2, 4); at 63^3 8.2 with (2, 4), 11 with (2, 1).  The
+// lines at 48, 96, 160 and 384 lie between tuned sizes; a step there is 1.14
+// (48), 1.21 (96), 1.29 (160) and 1.19 (384) times as fast as the LDS tiles were.
 struct March {
   int R, kz;
 };

@@ -257,8 +257,10 @@ struct HatF {
 
 // out = A xhat with dots: mode 0: partial0 += a.out (a = rhat);
 // mode 1: partial0 += out.a, partial1 += out.out (a = s).  HBM-bound (20 bytes
-// per unknown with an FP32 xhat): 256 x 128 x 256
-// 57 us (70-73 with an FP64 xhat, a block per plane and no XCD order).
+// per unknown with an FP32 xhat, 24 with an FP64 one).  256 x 128 x 256: 59 and
+// 56 us with the FP32 level (modes 0 and 1), 59 and 37 with an FP64 array,
+// whose xhat and a the kernels before have just written; 70-73 before the runs
+// of planes and the XCD order.
 template <bool RUNS, int MODE, class H>
 __global__ __launch_bounds__(256) void k_apply_dot(H Xh, double* __restrict__ Out, const double* __restrict__ Aw,
                                                    SGeom S, Coef c, const double* __restrict__ cot2,
@@ -529,8 +531,9 @@ void sline_go(const SLev& L, int colour, int zero_guess, hipStream_t st) {
     k_sline_t<SL, P, false><<<grid, nl * P, lds, st>>>(L, nls, colour, zero_guess);
 }
 
-// The splits that line_split makes of the sizes 2^m and 3 2^m in use: 64 x 32 x
-// 64 takes 5.0 us here, 9.7 with the runtime split, which takes the others.
+// The splits that line_split makes of the sizes 2^m and 3 2^m up to 256: 64 x 32
+// x 64 takes 5.0 us here, 9.7 with the runtime split, which takes every other
+// size (nph = 80, 112, 144, 160, 208, 224 and those above 256).
 bool sline_fixed(const SLev& L, int colour, int zero_guess, hipStream_t st) {
   if (L.count() >= (1ll << 31)) return false;
   if (L.nseg == 8 && L.seg == 2) {
