@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("method", ["mg", "mg_ir32"])
-@pytest.mark.parametrize("order,n", [(2, 2), (2, 8), (2, 16), (6, 4), (6, 9)])
+@pytest.mark.parametrize("order,n", [(2, 2), (2, 8), (2, 12), (6, 4), (6, 9)])
 def test_cartesian(order, n, method):
     say(f"single level: {method} order {order} n {n}")
     g = 1 if order == 2 else 3
